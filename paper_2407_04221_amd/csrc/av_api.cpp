@@ -320,6 +320,23 @@ av_status group_order_init(av_batch_t b) {
     return upload(&b->d_cost, std::vector<uint32_t>(size_t(B), 0u));
 }
 
+// The probe tables and merged entries of the group engine and the wave engine's one-wave form.
+av_status upload_group_tables(av_batch_t b) {
+    const av_config &c = b->cfg;
+    std::vector<uint32_t> tab, gm;
+    compile_group_tables(b->prog, c.height, c.width, c.channels,
+                         c.rule_mode == AV_RULES_SEQUENTIAL ? c.channels + 1 : c.channels,
+                         c.max_pat_h, tab, b->dprog.gtab_stride, gm, b->dprog.gmatch_stride);
+    if (av_status st = upload(&b->dprog.gtab, tab)) return st;
+    return upload(&b->dprog.gmatch, gm);
+}
+
+bool solo_takes(av_batch_t b, bool control, bool random) {
+    const av_config &c = b->cfg;
+    return solo_eligible(c.height, c.width, c.channels, b->prog.rules_per_set, c.max_pat_h,
+                         c.max_pat_w, c.rule_mode == AV_RULES_SEQUENTIAL, control, random);
+}
+
 // Copies of the batch step number: one per launch unit (at most one per environment, and
 // the lane16 engine's last workgroup may hold up to three waves past the batch), plus slack.
 int step_copies(int B) { return B + 8; }
@@ -517,13 +534,10 @@ av_status av_load_rules(av_batch_t b, int32_t R, const int32_t *shape, const int
     b->dprog.rvote_stride = b->prog.rvote_stride;
     b->dprog.any_reward = b->prog.any_reward;
     if (b->plain_engine == AV_ENGINE_GROUP) {
-        std::vector<uint32_t> tab;
-        std::vector<uint32_t> gm;
-        compile_group_tables(b->prog, c.height, c.width, c.channels, c.max_pat_h, tab,
-                             b->dprog.gtab_stride, gm, b->dprog.gmatch_stride);
-        if (av_status st = upload(&b->dprog.gtab, tab)) return st;
-        if (av_status st = upload(&b->dprog.gmatch, gm)) return st;
+        if (av_status st = upload_group_tables(b)) return st;
         if (av_status st = group_order_init(b)) return st;
+    } else if (b->plain_engine == AV_ENGINE_WAVE && solo_takes(b, false, false)) {
+        if (av_status st = upload_group_tables(b)) return st;
     }
     if (b->plain_engine == AV_ENGINE_ROWS) {
         compile_rows(b->prog, c.channels, b->rprog);
@@ -669,6 +683,8 @@ av_status av_set_rule_control(av_batch_t b, const int32_t *limit, const uint8_t 
         b->lane16_ctl = true;
         b->engine = AV_ENGINE_LANE16;
     } else if (on_wave) {
+        if (!b->dprog.gtab && solo_takes(b, true, random))
+            if (av_status st = upload_group_tables(b)) { free_control(b); return st; }
         b->engine = AV_ENGINE_WAVE;
     } else {
         b->engine = AV_ENGINE_GENERIC;

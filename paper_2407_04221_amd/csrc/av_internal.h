@@ -96,9 +96,9 @@ struct DeviceProgram {
     uint32_t *rvote = nullptr;
     int32_t rules_per_set = 0, match_stride = 0, vote_stride = 0, rvote_stride = 0;
     int32_t any_reward = 0;           // some rule of some set pays a nonzero reward
-    // group engine only (k_group.hip): per set, the probe table and the channel vote lists'
-    // rule ranges, gtab_stride words each, and the input entries merged per plane row,
-    // gmatch_stride words each
+    // group engine (k_group.hip) and the wave engine's one-wave form (k_solo.hip) only: per set,
+    // the probe table and the channel vote lists' rule ranges, gtab_stride words each, and the
+    // input entries merged per plane row, gmatch_stride words each
     uint32_t *gtab = nullptr;
     int32_t gtab_stride = 0;
     uint32_t *gmatch = nullptr;
@@ -267,8 +267,9 @@ bool group_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int m
 // The group engine's per-set tables (probe rows of the loaded rules, rule ranges of the
 // channel vote lists) for maps of H x W with patterns of up to max_pat_h rows, laid out as
 // the kernel keeps them in LDS, and its input entries merged per plane row (gm, gm_stride
-// words per set).
-void compile_group_tables(const GenericProgram &p, int H, int W, int C, int max_pat_h,
+// words per set).  lists: channels with a vote list to index (C, or C + 1 with the force plane
+// in sequential rule order).
+void compile_group_tables(const GenericProgram &p, int H, int W, int C, int lists, int max_pat_h,
                           std::vector<uint32_t> &tab, int &stride, std::vector<uint32_t> &gm,
                           int &gm_stride);
 hipError_t launch_group_step(const StepArgs &a, hipStream_t s);
@@ -281,5 +282,10 @@ long long device_wave_slots();
 size_t wave_lds_bytes(int H, int W, int C, int rules_per_set, bool control = false,
                       bool random = false);
 hipError_t launch_wave_step(const StepArgs &a, hipStream_t s);
+// The wave engine's one-wave form (k_solo.hip): sequential rule order and rule application
+// control on maps of up to 32 x 32; launch_wave_step takes it when the program has its tables.
+bool solo_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int max_pat_w,
+                   bool sequential, bool control, bool random);
+hipError_t launch_solo_step(const StepArgs &a, hipStream_t s);
 
 }  // namespace av
