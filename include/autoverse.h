@@ -70,7 +70,10 @@ typedef enum {
                                across lanes with DPP, the rule set compiled into the kernel */
     AV_ENGINE_WAVE = 3,     /* one environment per workgroup, map rows in LDS; 4 to 64
                                groups of lanes (as many as the batch's size leaves room for)
-                               match that many of its rules at once */
+                               match that many of its rules at once.  On maps of up to 32 x 32
+                               sequential rule order and rule application control run the group
+                               engine's kernel in those modes, one wave per environment, where
+                               its working set fits (av_step_n_static never does) */
     AV_ENGINE_ROWS = 4,     /* one environment per 64-lane wave, map row y in lane y,
                                planes in the workgroup's LDS; one lane per rule tests every
                                rule's rarest entries at once, so only rules that can match
@@ -81,18 +84,17 @@ typedef enum {
                                of H + 16 rows plus R + 4 match planes of H + 32 rows (4 bytes
                                per row for W <= 32, else 8), 36 bytes per rule and 96 more;
                                no rule application control */
-    AV_ENGINE_GROUP = 5     /* one environment per 64-lane wave, no barriers: 4 groups of 16
-                               lanes, lane y of each owning map row y (and row y + 16 on maps
-                               of 17 to 32 rows), group g matching rules g, g + 4, ...; input
-                               entries are merged per pattern row, every rule's first four
-                               merged entries are tested in one round of LDS reads, and only
-                               rules that pass somewhere read the rest.  After launches of 64 steps or more it measures each
+    AV_ENGINE_GROUP = 5     /* one environment per 64-lane wave, no barriers: eight lanes per
+                               rule, eight rules at once; within a launch only anchors near
+                               cells that changed since the step before are tested again; input
+                               entries are merged per pattern row, every rule is probed with
+                               four or eight of them, and only rules that keep an anchor read
+                               the rest.  After launches of 64 steps or more it measures each
                                environment's cycles and deals environments to workgroups so that
                                the slowest ones do not share a SIMD (results never depend on
                                the order; not while the stream is captured).  Needs parallel
                                rule order, H, W <= 32,
-                               (max_rules + 4) x max_pat_h x max_pat_w <= 254, at most 8
-                               channels per lane group and, within 64 KiB of LDS, C + 1 planes
+                               (max_rules + 4) x max_pat_h x max_pat_w <= 254 and, within 64 KiB of LDS, C + 1 planes
                                and R + 4 match planes of HR + max_pat_h - 1 rows (rounded up to
                                4), 3 C rows of HR, 12 words per rule plus 12, and C (R + 6)
                                words, 4 bytes each (HR = 16, or 32 on maps of 17 to 32 rows);

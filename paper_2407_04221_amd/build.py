@@ -12,7 +12,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["av_api.cpp", "av_search.cpp", "k_generic.hip", "k_wave.hip", "k_rows.hip", "k_observe.hip",
            "k_mutate.hip", "k_search.hip", "jit.cpp", "lane16_jit.cpp", "av_static.cpp",
-           "k_group.hip", "k_solo.hip"]
+           "k_group.hip"]
 TEMPLATE = "lane16_kernel.hip"          # compiled at run time, per rule set, with hipRTC
 # Device code is built without packed-FP32 instructions.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",

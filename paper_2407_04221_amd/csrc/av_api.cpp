@@ -103,7 +103,6 @@ void free_device_program(av_batch_t b) {
     dev_free(b->dprog.vote);
     dev_free(b->dprog.rvote);
     dev_free(b->dprog.gtab);
-    dev_free(b->dprog.gmatch);
     b->dprog = DeviceProgram{};
     dev_free(b->d_rows);
     b->d_rows = nullptr;
@@ -320,20 +319,19 @@ av_status group_order_init(av_batch_t b) {
     return upload(&b->d_cost, std::vector<uint32_t>(size_t(B), 0u));
 }
 
-// The probe tables and merged entries of the group engine and the wave engine's one-wave form.
+// The group kernel's tables (group engine, and the wave engine's batches that take the kernel).
 av_status upload_group_tables(av_batch_t b) {
     const av_config &c = b->cfg;
-    std::vector<uint32_t> tab, gm;
+    std::vector<uint32_t> tab;
     compile_group_tables(b->prog, c.height, c.width, c.channels,
                          c.rule_mode == AV_RULES_SEQUENTIAL ? c.channels + 1 : c.channels,
-                         c.max_pat_h, tab, b->dprog.gtab_stride, gm, b->dprog.gmatch_stride);
-    if (av_status st = upload(&b->dprog.gtab, tab)) return st;
-    return upload(&b->dprog.gmatch, gm);
+                         c.max_pat_h, tab, b->dprog.gtab_stride, b->dprog.gentry_words);
+    return upload(&b->dprog.gtab, tab);
 }
 
-bool solo_takes(av_batch_t b, bool control, bool random) {
+bool group_takes_mode(av_batch_t b, bool control, bool random) {
     const av_config &c = b->cfg;
-    return solo_eligible(c.height, c.width, c.channels, b->prog.rules_per_set, c.max_pat_h,
+    return group_mode_eligible(c.height, c.width, c.channels, b->prog.rules_per_set, c.max_pat_h,
                          c.max_pat_w, c.rule_mode == AV_RULES_SEQUENTIAL, control, random);
 }
 
@@ -536,7 +534,7 @@ av_status av_load_rules(av_batch_t b, int32_t R, const int32_t *shape, const int
     if (b->plain_engine == AV_ENGINE_GROUP) {
         if (av_status st = upload_group_tables(b)) return st;
         if (av_status st = group_order_init(b)) return st;
-    } else if (b->plain_engine == AV_ENGINE_WAVE && solo_takes(b, false, false)) {
+    } else if (b->plain_engine == AV_ENGINE_WAVE && group_takes_mode(b, false, false)) {
         if (av_status st = upload_group_tables(b)) return st;
     }
     if (b->plain_engine == AV_ENGINE_ROWS) {
@@ -683,7 +681,7 @@ av_status av_set_rule_control(av_batch_t b, const int32_t *limit, const uint8_t 
         b->lane16_ctl = true;
         b->engine = AV_ENGINE_LANE16;
     } else if (on_wave) {
-        if (!b->dprog.gtab && solo_takes(b, true, random))
+        if (!b->dprog.gtab && group_takes_mode(b, true, random))
             if (av_status st = upload_group_tables(b)) { free_control(b); return st; }
         b->engine = AV_ENGINE_WAVE;
     } else {

@@ -96,13 +96,11 @@ struct DeviceProgram {
     uint32_t *rvote = nullptr;
     int32_t rules_per_set = 0, match_stride = 0, vote_stride = 0, rvote_stride = 0;
     int32_t any_reward = 0;           // some rule of some set pays a nonzero reward
-    // group engine (k_group.hip) and the wave engine's one-wave form (k_solo.hip) only: per set,
-    // the probe table and the channel vote lists' rule ranges, gtab_stride words each, and the
-    // input entries merged per plane row, gmatch_stride words each
+    // group kernel only (k_group.hip): per set a table of gtab_stride words: the probe rows and
+    // the channel vote lists' rule ranges, the input entries merged per plane row (gentry_words)
+    // and the vote lists
     uint32_t *gtab = nullptr;
-    int32_t gtab_stride = 0;
-    uint32_t *gmatch = nullptr;
-    int32_t gmatch_stride = 0;
+    int32_t gtab_stride = 0, gentry_words = 0;
 };
 
 // Rule application control (paper Sec. 2.1.1): per loaded rule a cap on the matches applied
@@ -264,14 +262,15 @@ hipError_t launch_rows_step(const StepArgs &a, const uint32_t *words, int set_wo
 // The group engine (k_group.hip): one environment per wave, its rules dealt to 2 or 4 groups
 // of lanes; parallel rule order, no rule application control.
 bool group_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int max_pat_w);
-// The group engine's per-set tables (probe rows of the loaded rules, rule ranges of the
-// channel vote lists) for maps of H x W with patterns of up to max_pat_h rows, laid out as
-// the kernel keeps them in LDS, and its input entries merged per plane row (gm, gm_stride
-// words per set).  lists: channels with a vote list to index (C, or C + 1 with the force plane
-// in sequential rule order).
+// Sequential rule order or rule application control (the wave engine's batches) on the same kernel,
+// maps of up to 32 x 32; launch_wave_step takes it when the program has its tables.
+bool group_mode_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int max_pat_w,
+                         bool sequential, bool control, bool random);
+// The kernel's per-set tables for maps of H x W with patterns of up to max_pat_h rows (laid out
+// as the kernel keeps them in LDS).  lists: channels with a vote list (C, or C + 1 with the force
+// plane in sequential rule order).
 void compile_group_tables(const GenericProgram &p, int H, int W, int C, int lists, int max_pat_h,
-                          std::vector<uint32_t> &tab, int &stride, std::vector<uint32_t> &gm,
-                          int &gm_stride);
+                          std::vector<uint32_t> &tab, int &stride, int &entry_words);
 hipError_t launch_group_step(const StepArgs &a, hipStream_t s);
 
 // Wave slots of the current device (8 waves per SIMD, 4 SIMDs per CU; 0 if it cannot be
@@ -282,10 +281,5 @@ long long device_wave_slots();
 size_t wave_lds_bytes(int H, int W, int C, int rules_per_set, bool control = false,
                       bool random = false);
 hipError_t launch_wave_step(const StepArgs &a, hipStream_t s);
-// The wave engine's one-wave form (k_solo.hip): sequential rule order and rule application
-// control on maps of up to 32 x 32; launch_wave_step takes it when the program has its tables.
-bool solo_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int max_pat_w,
-                   bool sequential, bool control, bool random);
-hipError_t launch_solo_step(const StepArgs &a, hipStream_t s);
 
 }  // namespace av

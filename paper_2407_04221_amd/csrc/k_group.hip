@@ -1,648 +1,1199 @@
 // group engine: one environment per wave, its rules dealt to groups of lanes.
 //
-// The wave's 64 lanes form G = 4 groups of 16 lanes; lane y of every group owns map row y (a
-// 32-bit word, bit x = column x) and, on maps of 17 to 32 rows, row y + 16 too (HR = 16 or 32
-// rows a group covers), and group g matches rules g, g + G, g + 2G, ...  One workgroup is one
-// wave, so a step needs no barrier: the wave's LDS operations take effect in the order it issues
-// them.
+// Lane y of each of the wave's four groups of 16 lanes owns map row y (a 32-bit word, bit x =
+// column x) and, on maps of 17 to 32 rows, row y + 16 too (HR = 16 or 32 rows).  One workgroup is
+// one wave, so a step needs no barrier: the wave's LDS operations take effect in the order it
+// issues them.  The wave engine (k_wave.hip) runs the same kernel in its other modes: sequential
+// rule order (SEQ) and rule application control (CTL).
 //
-// The four built-in moves are computed in registers from the lanes' own rows of the player,
-// wall and force planes and the rows next to them (DPP row shifts within the 16-lane groups;
-// with two rows a lane, the rows 15 and 16 meet across the lanes' two words); the player and
-// wall rows stay in registers from step to step unless a loaded rule wrote those planes.  A rule's input entries are merged per plane
-// row (one LDS read tests every specified column of a pattern row, up to 8); each loaded
-// rule's first four merged entries sit in a probe table (held in registers for the launch when
-// a group has at most two rules, else read at the start of each step), so the probe of every
-// loaded rule is one round of LDS reads with no branch between the rules; only rules that
-// pass it somewhere read the rest of their entries, and only channels that received votes are
-// rewritten.
+// What bounds it: with four waves per SIMD the VALU work of testing pattern entries, with one wave
+// per SIMD the chain of dependent LDS round trips of a step, and a launch lasts as long as its
+// slowest environment.  So a step tests no more than it has to:
+//   - only anchors whose pattern can reach a cell that changed since the rule was last tested
+//     are tested again; a rule's other matches stand (M holds them from step to step).  Most
+//     steps move a player and its force, a few rows of the map, so
+//   - the rows to test are a window: eight lanes per rule, so eight rules at once, one row a lane
+//     when the window has at most 8 rows, else every row of the map (two or four a lane: what an
+//     entry's test costs beside its rows is shared by them);
+//   - a rule is probed with four merged entries (one LDS read tests every specified column of a
+//     pattern row), or eight, those that accept the fewest cells first, and only rules that still
+//     hold an anchor are finished, dealt to the octets as they come up.
+// Within a launch only: a launch's first step, and a step after a reset, tests every anchor.
+//
+// Measured (MI355X, one rule set per environment, 100 steps, against the form that tested every
+// anchor of every step with 16 lanes per rule and OR-ed votes before counting them): 1024 maps of
+// 16 x 16 with 8 rules planted on the first map 260 -> 200 us, with dense rules 24.6 -> 9.0 us per
+// step; 4096 of 32 x 32 with 16 rules planted 1632 -> 1239 us, dense 86 -> 42 us per step, random
+// rules 7.7 -> 6.6; one step of those with its observation 42.9 -> 32.7 us.  Against k_wave.hip's
+// several waves per environment: 777 maps of 23 x 19, sequential order, 50 steps 1760 -> 805 us;
+// 1024 of 32 x 32 with every rule capped at a random site and inhibiting the next, 50 steps
+// 15.8 -> 1.04 ms.
 //
 // LDS (32-bit rows):
 //   P    [C+1][PR]     the map and the force plane (channel C); PR = HR + ph - 1 rounded up to
 //                      4 rows (ph: the largest pattern's rows), so a lane reads row y + i of
 //                      any pattern entry without a bounds test (rows H .. PR - 1 stay zero)
-//   M    [R+4][PR]     match planes of the rules that fired, row y at ph - 1 + y: the zero rows
-//                      above let a vote read match row y - i without a test
-//   PL, MI [C][HR]     per stored channel, the OR of the +1 and of the -1 votes
-//   I0   [C][HR]       the initial rows, for resets
-//   PT   [R+5][12]     probe table: per loaded rule its first eight merged entries, its
-//                      anchor rows and columns, where its entries and its votes are and the
-//                      channels it votes on (row R + 4: zeros,
-//                      read by groups with fewer rules than others)
-//   RS   [C][R+4]      per channel and rule, the range of the rule's votes in the channel's
-//                      vote list (for exact recounts)
-//   RM   [C][2]        per channel, the 64-bit mask of the rules with votes in that list
-//   program            (when it fits, see the launcher) the environment's rule headers, input
-//                      merged entries, rule-major votes and channel-major vote lists
+//   M    [R+5][PR]     match planes, row y at ph - 1 + y: the zero rows above let a vote read
+//                      match row y - i without a test (plane R + 4: zeros, read by votes past the
+//                      end of a list); MV [R+4][PR] the same after control (CTL; else M)
+//   DR   [HR]          anchors to test, Q [R][HR] a window's matches
+//   the head of the set's table:
+//   PT   [R+5][12]     per rule its first four merged entries, anchor rows and columns, place of
+//                      its entries, reward, voted channels, its next four entries (row R + 4:
+//                      zeros, no anchors)
+//   RS   [NC][R+4]     per channel and rule, the place and number of the rule's votes in the
+//                      channel's list and how many are minus votes (NC: C, or C + 1 in sequential
+//                      order, where later rules read the force plane)
+//   CT   [R+4][3]      control: the rule's cap and its inhibitors' mask
+//   KEY  [H][W|1]      random site order: the step's index channel (32 words of slack)
+//   the rest of the table, in LDS as far as it fits (see the launcher): GM the merged entries,
+//                      CV the vote lists by channel
 //
-// Per step (paper Sec. 2.1, Sec. 2.1.1, Sec. 2.2.1):
+// Per step (paper Sec. 2.1, Sec. 2.1.1, Sec. 2.2.1), parallel rule order:
 //   force  F[y] = the player row moved one cell toward the action (group 0 writes it);
 //   moves  right P & (F >> 1) & ~(W >> 1), left F & ~W & (P >> 1), down P & F' & ~W', up
-//          F & ~W & P' (primes: the next row); their votes on the player plane are OR-ed in
-//          registers (-1 on the source cell, +1 on the target);
-//   match  per loaded rule, AND over its specified entries of plane row y + i shifted right by j,
-//          complemented for must-be-0, within the valid-anchor mask (the entries of one plane
-//          row i share its LDS read); a group leaves a rule as soon as no lane of the group has
-//          an anchor left;
-//   votes  a rule that fired stores its match plane and ORs match row y - i, shifted left by
-//          j, into the plus or minus row of each nonzero K_O = O - I entry's channel;
-//   write  group g rewrites channels g, g + G, ...: new = (old | plus) & ~minus where no cell
-//          got votes of both signs; a channel with such cells is recounted exactly with one
-//          bit-sliced counter over every fired rule's votes: new = (old + #plus > #minus);
+//          F & ~W & P' (primes: the next row), in registers: the player and wall rows stay in
+//          registers from step to step unless a loaded rule wrote those planes;
+//   match  probe and finish over the window; a rule's new match plane is its old one outside the
+//          tested anchors and the window's matches inside;
+//   control (CTL) the fired rules in index order: matches whose patch overlaps an applied match of
+//          an inhibiting rule are dropped, then at most `cap` kept, those first in row-major order
+//          or with the largest keys;
+//   write  the channels the fired rules voted on, eight at a time, one per octet: one bit-sliced
+//          counter over every fired rule's votes on the channel: new = (old + #plus > #minus);
 //   end    done when no player bit is left or the counter reaches L; reward = sum over fired
 //          rules of reward * popcount; done environments return to their initial rows.
-// Parallel rule order only, without rule application control.
+// Sequential rule order: the moves one after another in registers; then every rule is matched and,
+// in order, each rule that matches applies (after its control) and writes, and the rules behind it
+// are matched again where its changes reach.  The result is that of applying every rule in turn,
+// at one round per rule that applies instead of one per rule.
+//
+// A cap in random order: every lane takes eight cells of each of its rows (cells 8 g + i of group
+// g) and holds their keys, 0 where the rule does not match (a key is never 0: its low bits are the
+// rank 4095 - pos, and pos is at most 1023), so the wave holds every match's key in registers.  Up
+// to four matches are kept by as many maxima over the wave; more by the threshold T with exactly
+// `cap` keys at or above it, found bit by bit from the top (one ballot per held key and bit; keys
+// never tie).
 #include <algorithm>
+#include <type_traits>
 
-#include "group_common.h"
+#include "av_internal.h"
+#include "philox.h"
+
+#define AV_INLINE __attribute__((always_inline))
 
 namespace av {
 namespace {
 
-constexpr int kMaxRulesPerGroup = 16;   // loaded and built-in rules per group, at most
-constexpr int kMaxChanPerGroup = 8;     // stored channels a group writes, at most
-constexpr int kShortLaunch = 16;        // launches of fewer steps: SHORT kernels, program in
-                                        // global memory
+constexpr int kHq = 16;                 // lanes of a group
+constexpr int kG = 4;                   // groups of a wave
+constexpr int kProbeEntries = 4;        // merged entries of a rule tested in one round
+constexpr int kProbeWords = 12;         // probe table row: entries 0-3, anchor word, match
+                                        // offset | count << 16, reward, voted channels, entries
+                                        // 4-7
+// Input entries merged per plane row: o | jb << 12 | zero << 16 | one << 24 tests row o + y of the
+// planes (o = c * PR + i: pattern row i of plane c) at the pattern columns 8 jb + j, j < 8: a cell
+// of a column in `zero` must be 0, of a column in `one` must be 1.  kPassEntry tests no column (it
+// passes everywhere).
+constexpr uint32_t kPassEntry = 0u;
+constexpr int kMaxEntryOffset = 4095;
+constexpr uint32_t kMoreEntries = 1u << 16;   // of an anchor word: more entries than the probe's eight
+// Votes of a channel's list: byte offset of the rule's match row y - i from that of row y of rule
+// 0 (16 bits) | j << 16 | bit 31 for a minus vote.
+constexpr uint32_t kMinusVote = 0x80000000u;
+constexpr size_t kCuLds = 160 * 1024;   // LDS of a compute unit
+constexpr int kMaxChan = 32;            // channels with a vote list
+constexpr int kKeyCells = 8;            // cells of a row one lane holds keys for
+constexpr int kShortLaunch = 16;        // launches of fewer steps read the lists from memory
 
-// NR: rules a group holds (a bound on this launch's ceil(R / G)).
+// Words per plane row block: HR rows plus the pattern rows hanging below the last one,
+// rounded up to 4 (16-byte aligned table after the planes).
+__host__ __device__ constexpr int group_plane_words(int rows, int max_pat_h) {
+    return (rows + max_pat_h - 1 + 3) & ~3;
+}
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__host__ __device__ constexpr int key_stride(int W) { return W | 1; }
+// Words of a table's head (PT and RS), rounded up to 4.
+__host__ __device__ constexpr int group_head_words(int rules_per_set, int lists) {
+    return ((rules_per_set + 1) * kProbeWords + lists * rules_per_set + 3) & ~3;
+}
+// Map rows a lane group covers: its 16 lanes hold one row each, or two on maps of 17 to 32 rows.
+constexpr int group_rows(int H) { return H <= 16 ? 16 : 32; }
+
+__device__ inline uint32_t low_mask(int bits) { return bits >= 32 ? ~0u : ((1u << bits) - 1u); }
+__device__ inline uint32_t uniform(uint32_t v) {
+    return uint32_t(__builtin_amdgcn_readfirstlane(int(v)));
+}
+template <int CTRL>
+__device__ inline uint32_t dpp(uint32_t v) {
+    return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xF, 0xF, true));
+}
+
+// Orders the wave's LDS writes before its later LDS reads for the compiler (the hardware keeps
+// a wave's LDS operations in order, and no instruction comes of it).
+__device__ inline void lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// Copy n words (a multiple of 4, both 16-byte aligned) from global memory to LDS, four loads of a
+// lane in flight before its writes.
+__device__ inline void copy_to_lds(uint32_t *dst, const uint32_t *src, int n, int lane) {
+    u32x4 *const d = reinterpret_cast<u32x4 *>(dst);
+    const u32x4 *const s = reinterpret_cast<const u32x4 *>(src);
+    const int m = n >> 2;
+    for (int w0 = lane; w0 < m; w0 += 4 * 64) {
+        u32x4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int w = w0 + 64 * u;
+            v[u] = w < m ? s[w] : u32x4{0u, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int w = w0 + 64 * u;
+            if (w < m) d[w] = v[u];
+        }
+    }
+}
+
+// The groups of eight lanes with a lane in `bal`: bit w for lanes 8 w .. 8 w + 7.
+__device__ inline uint32_t octets_of(unsigned long long bal) {
+    bal |= bal >> 4;
+    bal |= bal >> 2;
+    bal |= bal >> 1;
+    bal &= 0x0101010101010101ull;                 // bit 0 of every byte, then side by side
+    return uint32_t((bal * 0x0102040810204080ull) >> 56);
+}
+
+// Inclusive prefix sum over the 16 lanes of a group.
+__device__ inline uint32_t group_prefix(uint32_t v) {
+    v += dpp<0x111>(v);                           // row_shr by 1, 2, 4, 8
+    v += dpp<0x112>(v);
+    v += dpp<0x114>(v);
+    v += dpp<0x118>(v);
+    return v;
+}
+// Sum over eight lanes, or the 16 of a group, in every lane.
+__device__ inline uint32_t octet_sum(uint32_t v) {
+    v += dpp<0x141>(v);                           // row_half_mirror: lanes 7 - i of 8
+    v += dpp<0xB1>(v);                            // lanes i ^ 1, i ^ 2
+    v += dpp<0x4E>(v);
+    return v;
+}
+__device__ inline uint32_t group_sum(uint32_t v) {
+    v = octet_sum(v);
+    return v + dpp<0x128>(v);                     // row_ror by 8
+}
+// Maximum over the wave (uniform).
+__device__ inline uint32_t wave_max(uint32_t v) {
+    v = max(v, dpp<0x128>(v));
+    v = max(v, dpp<0x124>(v));
+    v = max(v, dpp<0x122>(v));
+    v = max(v, dpp<0x121>(v));
+    uint32_t m = 0u;
+#pragma unroll
+    for (int gg = 0; gg < kG; ++gg)
+        m = max(m, uint32_t(__builtin_amdgcn_readlane(int(v), kHq * gg)));
+    return m;
+}
+// OR over the four groups (lanes y, y + 16, y + 32, y + 48).
+__device__ inline uint32_t groups_or(uint32_t v) {
+    const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = p[0] | p[1];
+    const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return q[0] | q[1];
+}
+
+// Rows y + 1 (next) and y - 1 (prev) of the rows a lane holds, 0 past the group's ends, RPL
+// of them (2: on maps of 17 to 32 rows a lane of a 16-lane group holds rows y and y + 16):
+// within each 16-row half a DPP row shift, across the halves a DPP row rotate (lane 15's next
+// row is lane 0's second row, lane 0's second row's previous row is lane 15's first).
+template <int RPL>
+__device__ inline void next_rows(const uint32_t (&v)[RPL], uint32_t (&n)[RPL], int y) {
+    if constexpr (RPL == 1) {
+        n[0] = dpp<0x101>(v[0]);
+    } else {
+        const uint32_t s0 = dpp<0x101>(v[0]), w1 = dpp<0x12F>(v[1]), s1 = dpp<0x101>(v[1]);
+        n[0] = y == kHq - 1 ? w1 : s0;
+        n[1] = s1;
+    }
+}
+template <int RPL>
+__device__ inline void prev_rows(const uint32_t (&v)[RPL], uint32_t (&p)[RPL], int y) {
+    if constexpr (RPL == 1) {
+        p[0] = dpp<0x111>(v[0]);
+    } else {
+        const uint32_t s0 = dpp<0x111>(v[0]), t1 = dpp<0x111>(v[1]), w0 = dpp<0x121>(v[0]);
+        p[0] = s0;
+        p[1] = y == 0 ? w0 : t1;
+    }
+}
+
+template <int RPL>
+__device__ inline bool any_row(const uint32_t (&v)[RPL]) {
+    uint32_t o = 0u;
+#pragma unroll
+    for (int h = 0; h < RPL; ++h) o |= v[h];
+    return o != 0u;
+}
+
+// Add the four one-bit planes x to the KB-bit bit-sliced counter q: carry-save adders make them a
+// 3-bit number, then one ripple add.
+template <int KB>
+__device__ inline void count4(uint32_t (&q)[KB], uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3) {
+    const uint32_t s1 = x0 ^ x1 ^ x2, c1 = (x0 & x1) | (x2 & (x0 ^ x1));   // weight 1, 2
+    const uint32_t s0 = s1 ^ x3, c2 = s1 & x3;                             // weight 1, 2
+    const uint32_t w2 = c1 ^ c2, w4 = c1 & c2;                             // weight 2, 4
+    uint32_t k = q[0] & s0;
+    q[0] ^= s0;
+    const uint32_t k1 = (q[1] & w2) | (k & (q[1] ^ w2));
+    q[1] = q[1] ^ w2 ^ k;
+    k = (q[2] & w4) | (k1 & (q[2] ^ w4));
+    q[2] = q[2] ^ w4 ^ k1;
+#pragma unroll
+    for (int b = 3; b < KB; ++b) {
+        const uint32_t kq = q[b] & k;
+        q[b] ^= k;
+        k = kq;
+    }
+}
+
 // RPL: map rows a lane holds: 2 on maps of 17 to 32 rows (lane y of a 16-lane group holds rows
 // y and y + 16), else 1.
 // NJ: columns a merged entry tests (3 when no pattern is wider, else 8).
-// PROG_LDS: the rule program is copied to LDS.  A compile-time choice, so that the program's
-// reads are LDS reads or global loads: a pointer that may be either makes every read a flat
-// load, which the LDS reads' waits then wait for as well.
-// SHORT: a launch of fewer than 16 steps (one step per observation), whose time is its set-up,
-// a step or a few and the final store, each a chain of memory round trips: every load of the
-// set-up is issued before its LDS writes (copy loops that wait for each load are one round
-// trip per 64 words), the final store forms its addresses anew, and the kernel may take 256
-// VGPRs, so nothing spills to scratch (at 128 a cold scratch reload on the path costs a round
-// trip).  Longer launches keep four waves per SIMD and the per-row set-up, whose step loop
-// measured faster (the set-up's code changes the loop's register assignment).
-// WIDE: a batch of at most two waves per SIMD (program in LDS), which four-wave occupancy
-// would not serve: the kernel may take 256 VGPRs, so nothing spills.
-template <int Hq, int RPL, int NR, int NJ, bool PROG_LDS, bool SHORT, bool WIDE>
-__global__ void __launch_bounds__(64, NR <= 8 ? ((SHORT || WIDE) ? 2 : 4) : 1) group_step(StepArgs a) {
-    static_assert(RPL == 1 || Hq == 16, "two rows a lane in 16-lane groups");
-    static_assert(!(SHORT && PROG_LDS), "short launches read the program from global memory");
-    static_assert(!(WIDE && (SHORT || !PROG_LDS)), "wide kernels are long launches with the program in LDS");
-    constexpr int G = 64 / Hq;
-    constexpr int HR = Hq * RPL;              // map rows a group covers
-    constexpr int kChunk = 4;                 // entries or votes of a rule read in one round
+// SEQ, CTL: sequential rule order, rule application control.
+// WHERE: kLds the table's lists are copied to LDS; kEntries the merged entries are, the votes are
+// read from memory; kGlobal both are.  A compile-time choice, so that the lists' reads are LDS
+// reads or global loads: a pointer that may be either makes every read a flat load, which the LDS
+// reads' waits then wait for as well.
+// WAVES: waves per SIMD the registers must leave room for.
+enum : int { kLds = 0, kEntries = 1, kGlobal = 2 };
+
+template <int RPL, int NJ, bool SEQ, bool CTL, int WHERE, int WAVES>
+__global__ void __launch_bounds__(64, WAVES) group_step(StepArgs a) {
+    constexpr int HR = kHq * RPL;                 // map rows a group covers
     extern __shared__ __align__(16) uint32_t lds[];
-    const int lane = int(threadIdx.x), g = lane / Hq, y = lane % Hq;
+    const int lane = int(threadIdx.x), g = lane / kHq, y = lane % kHq;
     const uint64_t t_start = __builtin_amdgcn_s_memtime();
     const int b = a.order ? a.order[blockIdx.x] : int(blockIdx.x);
     const int H = a.H, W = a.W, C = a.C, C1 = C + 1, Rt = a.prog.rules_per_set;
+    const int NC = SEQ ? C1 : C;
     // pattern rows beyond a lane's row: plane rows y + i and match rows y - i, i <= PAD, are
-    // read without a bounds test; rows of 4 words keep the probe table 16-byte aligned
+    // read without a bounds test
     const int PAD = a.max_pat_h - 1;
     const int PR = group_plane_words(HR, a.max_pat_h), MS = PR;
     const int s = a.per_env ? b : 0;
+    const int nl = Rt - kMoveRules;               // loaded rules
     // the lane's rows; past the map (rw false) their plane rows stay zero and are read freely
     // (row yr + i < PR), their anchors are masked off and they are never written
     int yr[RPL];
     bool rw[RPL];
 #pragma unroll
     for (int h = 0; h < RPL; ++h) {
-        yr[h] = y + Hq * h;
+        yr[h] = y + kHq * h;
         rw[h] = yr[h] < H;
     }
     const uint32_t wmask = low_mask(W);
+    const int head = group_head_words(Rt, NC);
 
-    uint32_t *P = lds;                             // [C1][PR]
-    uint32_t *M = P + C1 * PR;                     // [Rt][MS]
-    uint32_t *PL = M + Rt * MS;                    // [C][HR]
-    uint32_t *MI = PL + C * HR;                    // [C][HR]
-    uint32_t *I0 = MI + C * HR;                    // [C][HR] initial rows
-    uint32_t *PT = I0 + C * HR;                    // [Rt + 1][kProbeWords] probe table
-    uint32_t *RS = PT + (Rt + 1) * kProbeWords;    // [C][Rt] rule ranges of channel lists
-    uint32_t *RM = RS + C * Rt;                    // [C][2] rules with votes on each channel
-    uint32_t *lprog = RM + 2 * C;                  // program copy (PROG_LDS)
+    uint32_t *const P = lds;                       // [C1][PR]
+    uint32_t *const M = P + C1 * PR;               // [Rt + 1][MS]
+    uint32_t *const MV = CTL ? M + (Rt + 1) * MS : M;   // [Rt + 1][MS]
+    uint32_t *const DR = MV + (Rt + 1) * MS;       // [HR]
+    uint32_t *const Q = DR + HR;                   // [nl][HR]
+    uint32_t *const PT = Q + nl * HR;              // [Rt + 1][kProbeWords]
+    uint32_t *const RS = PT + (Rt + 1) * kProbeWords; // [NC][Rt]
+    uint32_t *const lists = PT + head;             // merged entries, votes (WHERE)
+    const int in_lds = WHERE == kLds ? a.prog.gtab_stride
+                                     : head + (WHERE == kEntries ? a.prog.gentry_words : 0);
+    uint32_t *const CT = PT + in_lds;              // [Rt][3] (CTL)
+    uint32_t *const KEY = CT + 3 * Rt;             // [H][key_stride(W)] + 32 (random order)
 
-    const uint32_t *ghdr = reinterpret_cast<const uint32_t *>(a.prog.hdr + size_t(s) * Rt);
-    const uint32_t *gment = a.prog.gmatch + size_t(s) * a.prog.gmatch_stride;
-    const uint32_t *gvent = a.prog.rvote + size_t(s) * a.prog.rvote_stride;
-    const uint32_t *gvl = reinterpret_cast<const uint32_t *>(a.prog.votes + size_t(s) * C1);
-    const uint32_t *gvote = a.prog.vote + size_t(s) * a.prog.vote_stride;
-    const int hdr_words = Rt * kHdrWords;
-    const uint32_t *hdrw = ghdr, *ment = gment, *vent = gvent, *vlw = gvl, *vote = gvote;
-    if constexpr (PROG_LDS) {
-        uint32_t *ph = lprog, *pm = ph + hdr_words, *pv = pm + a.prog.gmatch_stride;
-        uint32_t *pl = pv + a.prog.rvote_stride, *pc = pl + 2 * C1;
-        for (int w = lane; w < hdr_words; w += 64) ph[w] = ghdr[w];
-        for (int w = lane; w < a.prog.gmatch_stride; w += 64) pm[w] = gment[w];
-        for (int w = lane; w < a.prog.rvote_stride; w += 64) pv[w] = gvent[w];
-        for (int w = lane; w < 2 * C1; w += 64) pl[w] = gvl[w];
-        for (int w = lane; w < a.prog.vote_stride; w += 64) pc[w] = gvote[w];
-        hdrw = ph;
-        ment = pm;
-        vent = pv;
-        vlw = pl;
-        vote = pc;
-    }
+    const uint32_t *const gtab = a.prog.gtab + size_t(s) * a.prog.gtab_stride;
+    const uint32_t *const gm = WHERE == kGlobal ? gtab + head : lists;
+    const uint32_t *const cv = (WHERE == kLds ? lists : gtab + head) + a.prog.gentry_words;
+
+    copy_to_lds(PT, gtab, in_lds, lane);
     {
-        const int words = C1 * PR + Rt * MS + 3 * C * HR;   // (PT and RS are copied)
-        for (int w = lane; w < words; w += 64) lds[w] = 0u;
-    }
-
-    // the probe table and the rule ranges (built with the program: compile_group_tables)
-    {
-        const uint32_t *gt = a.prog.gtab + size_t(s) * a.prog.gtab_stride;
-        if constexpr (SHORT) copy_to_lds(PT, gt, a.prog.gtab_stride, lane);
-        else for (int w = lane; w < a.prog.gtab_stride; w += 64) PT[w] = gt[w];
-    }
-    const int nl = Rt - kMoveRules;               // loaded rules
-    const int nr = (nl - g + G - 1) / G;          // this group's loaded rule count
-    // (SHORT) lane l takes row l % H of channels l / H, l / H + 64 / H, ...
-    const int rcs = 64 / H;
-    if constexpr (SHORT) {
-        const int rcl = lane / H, rrow = lane - rcl * H;
-        auto load_rows = [&](const auto *st, const auto *in) {
-            for (int c0 = rcl; c0 < C; c0 += 4 * rcs) {
-                uint32_t sv[4], iv[4];
+        // planes and match planes: zero; then the map's rows.  Lane l takes row l % H of channels
+        // l / H, l / H + 64 / H, ..., four rows of a lane in flight
+        const int rcs = 64 / H, rcl = lane / H, rrow = lane - rcl * H;
+        auto zero = [&]() AV_INLINE {
+            u32x4 *const z = reinterpret_cast<u32x4 *>(lds);
+            const int words = int(DR - P) >> 2;
+            for (int w = lane; w < words; w += 64) z[w] = u32x4{0u, 0u, 0u, 0u};
+        };
+        auto load_rows = [&](const auto *st) AV_INLINE {
+            bool first = true;
+            for (int c0 = rcl; c0 - rcl < C; c0 += 4 * rcs) {
+                uint32_t sv[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int c = c0 + u * rcs;
-                    const size_t at = (size_t(c) * a.B + b) * H + rrow;
-                    sv[u] = c < C ? uint32_t(st[at]) : 0u;
-                    iv[u] = c < C ? uint32_t(in[at]) : 0u;
+                    sv[u] = rcl < rcs && c < C ? uint32_t(st[(size_t(c) * a.B + b) * H + rrow]) : 0u;
                 }
+                if (first) zero();
+                first = false;
+                lds_order();
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int c = c0 + u * rcs;
-                    if (c < C) {
-                        P[c * PR + rrow] = sv[u];
-                        I0[c * HR + rrow] = iv[u];
-                    }
+                    if (rcl < rcs && c < C) P[c * PR + rrow] = sv[u];
                 }
             }
         };
-        if (rcl < rcs) {
-            if (a.row_bytes == 2)
-                load_rows(static_cast<const uint16_t *>(a.state), static_cast<const uint16_t *>(a.init));
-            else
-                load_rows(static_cast<const uint32_t *>(a.state), static_cast<const uint32_t *>(a.init));
-        }
-    } else {
-#pragma unroll
-    for (int q = 0; q < kMaxChanPerGroup; ++q) {
-        const int c = g + G * q;
-#pragma unroll
-        for (int h = 0; h < RPL; ++h) {
-            if (c < C && rw[h]) {
-                const size_t at = (size_t(c) * a.B + b) * H + yr[h];
-                P[c * PR + yr[h]] = a.row_bytes == 2
-                                        ? uint32_t(static_cast<const uint16_t *>(a.state)[at])
-                                        : static_cast<const uint32_t *>(a.state)[at];
-                I0[c * HR + yr[h]] = a.row_bytes == 2
-                                         ? uint32_t(static_cast<const uint16_t *>(a.init)[at])
-                                         : static_cast<const uint32_t *>(a.init)[at];
-            }
+        if (a.row_bytes == 2) load_rows(static_cast<const uint16_t *>(a.state));
+        else load_rows(static_cast<const uint32_t *>(a.state));
+    }
+    if constexpr (CTL) {
+        for (int r = lane; r < Rt; r += 64) {
+            const size_t cr = size_t(s) * Rt + r;
+            CT[3 * r] = uint32_t(a.ctl.limit[cr]);
+            CT[3 * r + 1] = a.ctl.inhibit[cr * a.ctl.words];
+            CT[3 * r + 2] = a.ctl.words > 1 ? a.ctl.inhibit[cr * a.ctl.words + 1] : 0u;
         }
     }
-    }
-    __syncthreads();   // (one wave: orders the set-up's LDS writes before the step's reads)
     int t_env = a.t[b];
     const uint64_t nbase = a.nctr[b];
+    __syncthreads();   // (one wave: orders the set-up's LDS writes before the step's reads)
 
-    // entry e (merged per plane row) at this lane's row: OR-s into bad the anchors where a
-    // tested column does not hold the wanted value (the row moved right by the column's
-    // offset); a column's care and want bits sign-extended are all-ones masks
-    auto miss = [&](uint32_t e, uint32_t (&bad)[RPL]) {
-        uint32_t v[RPL];
+    // The window: eight lanes per rule (or channel), this lane in octet wo at place wl, at rows
+    // wr + 8 h (h < RP: one row, or FULL when the window is every row of the map).
+    constexpr int FULL = HR / 8;
+    // with four waves per SIMD (128 registers) probe rows stay in LDS and, with two rows a lane, a
+    // write of every row is made in two halves, or registers would spill
+    constexpr bool HELD = WAVES < 4, HALVES = RPL == 2 && WAVES == 4;
+    const int wo = lane >> 3, wl = lane & 7;
+    int wr = wl, r0 = 0;                          // r0: the window's first row
+    // four merged entries at the window's rows: the anchors m they leave.  A column's bits of an
+    // entry sign-extended are masks; what a column rejects is gathered unshifted over the four
+    // entries and moved right by the column's offset once (the cells that the shift would bring in
+    // from past the map's edge are no anchors)
+    auto entries4 = [&](const u32x4 &e4, auto &m) AV_INLINE {
+        constexpr int RP = sizeof(m) / sizeof(m[0]);
+        const uint32_t e[4] = {e4.x, e4.y, e4.z, e4.w};
+        uint32_t v[4][RP], bad[RP];
 #pragma unroll
-        for (int h = 0; h < RPL; ++h) {
-            v[h] = P[int(e & uint32_t(kMaxEntryOffset)) + yr[h]];
-            if constexpr (NJ > 3) v[h] >>= (e >> 9) & 24u;
+        for (int u = 0; u < 4; ++u) {
+#pragma unroll
+            for (int h = 0; h < RP; ++h) v[u][h] = P[int(e[u] & uint32_t(kMaxEntryOffset)) + wr + 8 * h];
         }
+        if constexpr (NJ > 3) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int h = 0; h < RP; ++h) v[u][h] >>= (e[u] >> 9) & 24u;
+        }
+#pragma unroll
+        for (int h = 0; h < RP; ++h) bad[h] = 0u;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const uint32_t want = uint32_t(int32_t(e << (7 - j)) >> 31);
-            const uint32_t care = uint32_t(int32_t(e << (15 - j)) >> 31);
+            uint32_t o[RP];
 #pragma unroll
-            for (int h = 0; h < RPL; ++h) bad[h] |= ((v[h] >> j) ^ want) & care;
+            for (int h = 0; h < RP; ++h) o[h] = 0u;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t zero = uint32_t(int32_t(e[u] << (15 - j)) >> 31);
+                const uint32_t one = uint32_t(int32_t(e[u] << (7 - j)) >> 31);
+#pragma unroll
+                for (int h = 0; h < RP; ++h) o[h] |= (v[u][h] & zero) | (~v[u][h] & one);
+            }
+#pragma unroll
+            for (int h = 0; h < RP; ++h) bad[h] |= o[h] >> j;
+        }
+#pragma unroll
+        for (int h = 0; h < RP; ++h) m[h] &= ~bad[h];
+    };
+    // table row of loaded rule i (none: row Rt, which has no anchors)
+    auto row_of = [&](int i) AV_INLINE { return PT + (i < nl ? kMoveRules + i : Rt) * kProbeWords; };
+    // the probe entries and anchor words of loaded rules wo and wo + 8, held for the launch (if HELD)
+    auto held = [&](int i, u32x4 &e, uint32_t &v) AV_INLINE {
+        const uint32_t *const row = row_of(i);
+        e = *reinterpret_cast<const u32x4 *>(row);
+        v = row[4];
+    };
+    u32x4 ha0, ha1;
+    uint32_t hav0, hav1;
+    if constexpr (HELD) {
+        held(wo, ha0, hav0);
+        held(8 + wo, ha1, hav1);
+    }
+    // probe of loaded rules w .. w + 7 (or w + 15) over the window, rule w + wo (and w + 8 + wo) by
+    // this lane's octet, among the anchors t: their first four entries and, where some rule keeps
+    // an anchor, the next four; where one still does, the window's rows so far go to Q: rules
+    // without more entries match there (hit), the others are returned (loaded rules).  (On crowded
+    // maps four entries leave most rules an anchor and eight leave few: the second four here cost
+    // half of what they cost in finish, which deals the rules out again.)
+    auto probe = [&](int w, bool two, const auto &t, uint64_t &hit) AV_INLINE -> uint64_t {
+        constexpr int RP = sizeof(t) / sizeof(t[0]);
+        uint64_t found = 0ull;
+        auto start = [&](uint32_t pv, uint32_t (&m)[RP]) AV_INLINE {
+#pragma unroll
+            for (int h = 0; h < RP; ++h)
+                m[h] = wr + 8 * h < int((pv >> 8) & 255u) ? t[h] & (~0u >> (pv & 255u)) : 0u;
+        };
+        auto keep = [&](int i, uint32_t pv, const uint32_t (&m)[RP], int at) AV_INLINE {
+            const unsigned long long bal = __builtin_amdgcn_ballot_w64(any_row<RP>(m));
+            if (!bal) return;
+            if (i < nl) {
+#pragma unroll
+                for (int h = 0; h < RP; ++h) Q[i * HR + wl + 8 * h] = m[h];
+            }
+            const unsigned long long more = bal & __builtin_amdgcn_ballot_w64((pv & kMoreEntries) != 0u);
+            hit |= uint64_t(octets_of(bal & ~more)) << at;
+            found |= uint64_t(octets_of(more)) << at;
+        };
+        const int i0 = w + wo, i1 = w + 8 + wo;
+        uint32_t m0[RP], m1[RP];
+        u32x4 e0, e1;
+        uint32_t v0, v1;
+        if (HELD && w == 0) {
+            e0 = ha0;
+            v0 = hav0;
+            e1 = ha1;
+            v1 = hav1;
+            // (opaque: the columns' masks, formed ahead of the step loop, would take the registers)
+            asm volatile("" : "+v"(e0), "+v"(e1));
+        } else {
+            held(i0, e0, v0);
+            held(i1, e1, v1);
+        }
+        start(v0, m0);
+        entries4(e0, m0);
+        if (two) {
+            start(v1, m1);
+            entries4(e1, m1);
+            if (!__builtin_amdgcn_ballot_w64(any_row<RP>(m0) || any_row<RP>(m1))) return 0ull;
+            e0 = *reinterpret_cast<const u32x4 *>(row_of(i0) + 8);
+            e1 = *reinterpret_cast<const u32x4 *>(row_of(i1) + 8);
+            entries4(e0, m0);
+            entries4(e1, m1);
+            keep(i0, v0, m0, w);
+            keep(i1, v1, m1, w + 8);
+        } else {
+            if (!__builtin_amdgcn_ballot_w64(any_row<RP>(m0))) return 0ull;
+            entries4(*reinterpret_cast<const u32x4 *>(row_of(i0) + 8), m0);
+            keep(i0, v0, m0, w);
+        }
+        lds_order();
+        return found;
+    };
+    // The entries from the ninth on of the first eight loaded rules of `cand`, one per octet, over
+    // the window; their matches go to Q.  Takes them out of cand; returns those
+    // that match somewhere.
+    auto finish = [&](uint64_t &cand, auto rp) AV_INLINE -> uint64_t {
+        constexpr int RP = decltype(rp)::value;
+        int i = nl;                               // the octet's rule
+        uint64_t left = cand;
+        for (int q = 0; q < 8 && left; ++q, left &= left - 1ull)
+            i = wo == q ? __builtin_ctzll(left) : i;
+        const uint64_t taken = cand & ~left;
+        cand = left;
+        const uint32_t meta = row_of(i)[5];
+        uint32_t m[RP];
+#pragma unroll
+        for (int h = 0; h < RP; ++h) m[h] = i < nl ? Q[(i < nl ? i : 0) * HR + wl + 8 * h] : 0u;
+        const int off = int(meta & 0xFFFFu), cnt = int(meta >> 16);
+        auto four = [&](int pos) AV_INLINE -> u32x4 {   // (reads stay inside the rule's entries)
+            const bool on = pos < cnt;
+            u32x4 x;
+            x.x = on ? gm[off + pos] : kPassEntry;
+            x.y = on ? gm[off + min(pos + 1, cnt - 1)] : kPassEntry;
+            x.z = on ? gm[off + min(pos + 2, cnt - 1)] : kPassEntry;
+            x.w = on ? gm[off + min(pos + 3, cnt - 1)] : kPassEntry;
+            return x;
+        };
+        u32x4 x = four(2 * kProbeEntries);
+        for (int pos = 2 * kProbeEntries; __builtin_amdgcn_ballot_w64(any_row<RP>(m) && pos < cnt);) {
+            pos += kProbeEntries;
+            const u32x4 nx = four(pos);
+            entries4(x, m);
+            x = nx;
+        }
+        if (i < nl) {
+#pragma unroll
+            for (int h = 0; h < RP; ++h) Q[i * HR + wl + 8 * h] = m[h];
+        }
+        const uint32_t f = octets_of(__builtin_amdgcn_ballot_w64(any_row<RP>(m)));
+        lds_order();
+        // the rules of the octets in f: the q-th of `taken` for bit q
+        uint64_t hit = 0ull;
+        int q = 0;
+        for (uint64_t tk = taken; tk; tk &= tk - 1ull, ++q)
+            hit |= ((f >> q) & 1u) ? tk & (0ull - tk) : 0ull;
+        return hit;
+    };
+
+    // Cells that changed since the rules were last tested (the lane's rows), and the anchors whose
+    // pattern can reach one (Dd): pw - 1 columns to the left and ph - 1 rows up.  Returns the rows
+    // that hold such an anchor.
+    uint32_t Dd[RPL];
+    auto spread = [&](const uint32_t (&D)[RPL]) AV_INLINE -> uint32_t {
+        uint32_t t[RPL];
+#pragma unroll
+        for (int h = 0; h < RPL; ++h) {
+            if constexpr (NJ == 3) {
+                t[h] = D[h] | (D[h] >> 1) | (D[h] >> 2);   // (a pattern is at most 3 wide)
+            } else {
+                t[h] = D[h];
+                for (int j = 1; j < a.max_pat_w; ++j) t[h] |= D[h] >> j;
+            }
+            Dd[h] = t[h];
+        }
+        for (int i = 1; i <= PAD; ++i) {
+            next_rows<RPL>(t, t, y);
+#pragma unroll
+            for (int h = 0; h < RPL; ++h) Dd[h] |= t[h];
+        }
+        uint32_t rows = 0u;
+#pragma unroll
+        for (int h = 0; h < RPL; ++h) {
+            rows |= uint32_t(__builtin_amdgcn_ballot_w64(Dd[h] != 0u) & 0xFFFFull) << (kHq * h);
+            if (g == 0) DR[yr[h]] = Dd[h];
+        }
+        lds_order();
+        return rows;
+    };
+    // the window for the anchors' rows; true: every row of the map (FULL rows a lane)
+    auto window = [&](uint32_t rows) AV_INLINE -> bool {
+        const int lo = __builtin_ctz(rows), hi = 31 - __builtin_clz(rows);
+        const bool all = hi - lo >= 8;
+        r0 = all ? 0 : min(lo, HR - 8);
+        wr = r0 + wl;
+        return all;
+    };
+    // rule r's new match plane: its matches so far outside the tested anchors (if `had`), the
+    // window's (if `hit`) inside; false when it is empty
+    auto settle = [&](int r, bool had, bool hit) AV_INLINE -> bool {
+        uint32_t m[RPL];
+#pragma unroll
+        for (int h = 0; h < RPL; ++h) {
+            m[h] = had ? M[r * MS + PAD + yr[h]] & ~Dd[h] : 0u;
+            const int l = yr[h] - r0;
+            // (the window of every row: r0 = 0 and HR rows)
+            if (hit && l >= 0 && l < HR) {
+                const uint32_t q = Q[(r - kMoveRules) * HR + l];
+                m[h] |= q & Dd[h];
+            }
+            M[r * MS + PAD + yr[h]] = m[h];
+        }
+        lds_order();
+        return __builtin_amdgcn_ballot_w64(any_row<RPL>(m)) != 0ull;
+    };
+
+    uint64_t live = 0ull;                         // the rules with matches in M
+    // Matches of loaded rules w and on against the map as it is, D holding at least the cells that
+    // changed since each of them was last matched: M and live.
+    auto match = [&](const uint32_t (&D)[RPL], int w) AV_INLINE {
+        const uint32_t rows = spread(D);
+        if (!rows) return;
+        uint64_t hit = 0ull;
+        auto scan = [&](const auto &t) AV_INLINE {
+            constexpr int RP = sizeof(t) / sizeof(t[0]);
+            uint64_t cand = 0ull;
+            for (int v = w; v < nl; v += 16) cand |= probe(v, v + 8 < nl, t, hit);
+            while (cand) hit |= finish(cand, std::integral_constant<int, RP>{});
+        };
+        if (window(rows)) {
+            uint32_t t[FULL];
+#pragma unroll
+            for (int h = 0; h < FULL; ++h) t[h] = DR[wr + 8 * h];
+            scan(t);
+        } else {
+            const uint32_t t[1] = {DR[wr]};
+            scan(t);
+        }
+        hit <<= kMoveRules;
+        for (uint64_t z = hit | (live >> (kMoveRules + w) << (kMoveRules + w)); z; z &= z - 1ull) {
+            const uint64_t bit = z & (0ull - z);
+            live = settle(__builtin_ctzll(z), live & bit, hit & bit) ? live | bit : live & ~bit;
         }
     };
-    // the anchors m of the lane's rows that pass four entries more
-    auto entries4 = [&](uint32_t e0, uint32_t e1, uint32_t e2, uint32_t e3, uint32_t (&m)[RPL]) {
-        uint32_t bad[RPL];
+
+    uint32_t have_keys = 0u;                      // (random order) passes of 64 blocks in KEY
+    // control of rule r, which fired on this step's map: drops inhibited matches (inhibitors among
+    // `applied`) and those above the cap; false when none is left.  Every group does the same
+    // work on all rows, but for the keys, which are split over the groups.  M keeps every match,
+    // MV gets those that apply.
+    auto control = [&](int r, uint64_t applied, uint64_t n) AV_INLINE -> bool {
+        uint32_t acc[RPL];
 #pragma unroll
-        for (int h = 0; h < RPL; ++h) bad[h] = 0u;
-        miss(e0, bad);
-        miss(e1, bad);
-        miss(e2, bad);
-        miss(e3, bad);
+        for (int h = 0; h < RPL; ++h) acc[h] = M[r * MS + PAD + yr[h]];
+        const int lim = int(uniform(CT[3 * r]));
+        const uint32_t pv = uniform(PT[r * kProbeWords + 4]);
+        const int hn = H + 1 - int((pv >> 8) & 255u), hm = W - 31 + int(pv & 255u);
+        uint64_t inh = (uint64_t(uniform(CT[3 * r + 1])) | (uint64_t(uniform(CT[3 * r + 2])) << 32)) & applied;
+        for (; inh; inh &= inh - 1) {
+            const int q = __builtin_ctzll(inh);
+            const uint32_t qv = uniform(PT[q * kProbeWords + 4]);
+            const int nq = H + 1 - int((qv >> 8) & 255u), mq = W - 31 + int(qv & 255u);
+            // anchors of q whose patch meets an hn-row patch at the lane's rows: rows
+            // y - nq + 1 .. y + hn - 1 (rows past the map are zero)
+            uint32_t o[RPL], t[RPL], u[RPL];
 #pragma unroll
-        for (int h = 0; h < RPL; ++h) m[h] &= ~bad[h];
+            for (int h = 0; h < RPL; ++h) o[h] = t[h] = u[h] = MV[q * MS + PAD + yr[h]];
+            for (int d = 1; d < hn; ++d) {
+                next_rows<RPL>(t, t, y);
+#pragma unroll
+                for (int h = 0; h < RPL; ++h) o[h] |= t[h];
+            }
+            for (int d = 1; d < nq; ++d) {
+                prev_rows<RPL>(u, u, y);
+#pragma unroll
+                for (int h = 0; h < RPL; ++h) o[h] |= u[h];
+            }
+#pragma unroll
+            for (int h = 0; h < RPL; ++h) {
+                uint32_t dil = o[h];
+                for (int d = 1; d < hm; ++d) dil |= o[h] >> d;
+                for (int d = 1; d < mq; ++d) dil |= o[h] << d;
+                acc[h] &= ~dil;
+            }
+        }
+        if (lim > 0) {
+            int inc[RPL], total = 0;              // matches up to and including the lane's rows
+#pragma unroll
+            for (int h = 0; h < RPL; ++h) {
+                inc[h] = int(group_prefix(uint32_t(__popc(acc[h])))) + total;
+                total = __builtin_amdgcn_readlane(inc[h], kHq - 1);
+            }
+            if (total > lim) {
+                if (!a.ctl.random) {
+#pragma unroll
+                    for (int h = 0; h < RPL; ++h) {
+                        // drop the row's last matches past the cap
+                        for (int over = min(inc[h] - lim, __popc(acc[h])); over > 0; --over)
+                            acc[h] &= ~(0x80000000u >> __builtin_clz(acc[h]));
+                    }
+                } else {
+                    // the keys of 512 cells per pass of the wave, made when first needed
+                    const int passes = (H * W + 511) / 512;
+                    if (!have_keys) {
+                        for (int p = 0; p < passes; ++p) {
+                            const int gi = 64 * p + lane;
+                            if (gi * 8 < H * W) {
+                                uint32_t u[8];
+                                philox_words(a.ctl.seed, n, uint64_t(b), 0, uint64_t(gi), u);
+                                int ky = (gi * 8) / W, kx = gi * 8 - ky * W;
+#pragma unroll
+                                for (int j = 0; j < 8; ++j) {
+                                    if (gi * 8 + j < H * W)
+                                        KEY[ky * key_stride(W) + kx] =
+                                            (u[j] & 0xFFFFF000u) | uint32_t(4095 - (gi * 8 + j));
+                                    ++kx;
+                                    if (kx == W) { kx = 0; ++ky; }
+                                }
+                            }
+                        }
+                        have_keys = 1u;
+                        lds_order();
+                    }
+                    uint32_t key[RPL][kKeyCells];
+#pragma unroll
+                    for (int h = 0; h < RPL; ++h) {
+                        const uint32_t *kr = KEY + min(yr[h], H - 1) * key_stride(W) + kKeyCells * g;
+                        const uint32_t f = acc[h] >> (kKeyCells * g);
+#pragma unroll
+                        for (int i = 0; i < kKeyCells; ++i)
+                            key[h][i] = kr[i] & uint32_t(int32_t(f << (31 - i)) >> 31);
+                    }
+                    uint32_t T = 0u;
+                    if (lim <= 4) {
+                        for (int got = 0; got < lim; ++got) {   // the next largest key
+                            uint32_t v = 0u;
+#pragma unroll
+                            for (int h = 0; h < RPL; ++h)
+#pragma unroll
+                                for (int i = 0; i < kKeyCells; ++i)
+                                    v = max(v, got == 0 || key[h][i] < T ? key[h][i] : 0u);
+                            T = wave_max(v);
+                        }
+                    } else {
+                        for (int bit = 31; bit >= 0; --bit) {
+                            const uint32_t t = T | (1u << bit);
+                            int at_least = 0;
+#pragma unroll
+                            for (int h = 0; h < RPL; ++h)
+#pragma unroll
+                                for (int i = 0; i < kKeyCells; ++i)
+                                    at_least += __popcll(__builtin_amdgcn_ballot_w64(key[h][i] >= t));
+                            if (at_least >= lim) T = t;
+                            if (at_least == lim) break;
+                        }
+                    }
+                    // each group's kept cells, OR-ed over the groups
+#pragma unroll
+                    for (int h = 0; h < RPL; ++h) {
+                        uint32_t keep = 0u;
+#pragma unroll
+                        for (int i = 0; i < kKeyCells; ++i)
+                            keep |= key[h][i] >= T ? 1u << i : 0u;
+                        acc[h] = groups_or(keep << (kKeyCells * g));
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < RPL; ++h) MV[r * MS + PAD + yr[h]] = acc[h];
+        lds_order();
+        return __builtin_amdgcn_ballot_w64(any_row<RPL>(acc)) != 0ull;
+    };
+
+    // New rows of the channels in `which`, eight at a time, one per octet, from the votes of the loaded
+    // rules in `fu` (uniform), whose match rows OR-ed are fm: only a window of rows gets votes, and
+    // with eight rows or fewer eight channels are written at once.  With `moves` the four moves'
+    // votes on the player plane count too (two each, from their match rows; pn: its rows by those
+    // votes alone).  A vote reads its rule's match row y - i shifted by j; a minus vote adds the
+    // complement of its cells, so one counter takes old + #plus + (#minus entries - #minus votes),
+    // and a cell is set, old + #plus - #minus >= 1, where it reaches 1 + #minus entries.  The
+    // counters have 4, 6 or 8 bits by the most votes a channel of the round gets (a list holds at
+    // most 254).  Returns in ch the cells that the votes changed.
+    auto write = [&](uint32_t which, uint64_t fu, const uint32_t (&fm)[RPL], bool moves,
+                     const uint32_t (&pn)[RPL], uint32_t (&ch)[RPL]) AV_INLINE {
+        auto rows_of = [&](auto rp, bool half) AV_INLINE {
+            constexpr int RP = decltype(rp)::value;
+            const uint32_t *const mw = MV + wr;   // the lane's row of match plane 0, less PAD rows
+            uint32_t cw[RP];
+#pragma unroll
+            for (int h = 0; h < RP; ++h) cw[h] = 0u;
+            uint32_t left = which;
+            while (left) {
+                int c = -1;
+                const uint32_t all = left;
+                for (int q = 0; q < 8 && left; ++q, left &= left - 1u)
+                    c = wo == q ? __builtin_ctz(left) : c;
+                const bool on = c >= 0, mv = !SEQ && moves && c == kChPlayer;
+                const int cc = on ? c : 0;
+                const uint32_t *const rs = RS + cc * Rt;
+                uint32_t old[RP];
+#pragma unroll
+                for (int h = 0; h < RP; ++h) old[h] = P[cc * PR + wr + 8 * h];
+                lds_order();
+                if (!SEQ && moves && (((all & ~left) >> kChPlayer) & 1u) && g == 0) {
+#pragma unroll
+                    for (int h = 0; h < RPL; ++h)     // rows without votes of loaded rules
+                        if (rw[h] && (!half || (yr[h] >= r0 && yr[h] < r0 + 8 * RP)))
+                            P[kChPlayer * PR + yr[h]] = pn[h];
+                }
+                lds_order();
+                // votes and minus votes of the fired rules on c, the octet's lanes adding up theirs
+                uint32_t w = rs[__builtin_ctzll(fu)], sum;
+                if (fu & (fu - 1ull)) {
+                    sum = 0u;
+                    for (int q = 0; q < nl; q += 8) {
+                        const int r = kMoveRules + q + wl;
+                        const uint32_t v = rs[min(r, Rt - 1)];
+                        sum += r < Rt && ((fu >> r) & 1ull) ? ((v >> 16) & 255u) | ((v >> 24) << 16) : 0u;
+                    }
+                    sum = octet_sum(sum);
+                } else {
+                    sum = ((w >> 16) & 255u) | ((w >> 24) << 16);
+                }
+                sum = on ? sum : 0u;
+                const int total = int(sum & 0xFFFFu) + (mv ? 2 * kMoveRules : 0);
+                const uint32_t need = 1u + (sum >> 16) + (mv ? kMoveRules : 0);   // 1 + #minus entries
+                auto run = [&](auto kb) AV_INLINE {
+                    constexpr int KB = decltype(kb)::value;
+                    uint32_t cnt[RP][KB];
+#pragma unroll
+                    for (int h = 0; h < RP; ++h) {
+#pragma unroll
+                        for (int q = 1; q < KB; ++q) cnt[h][q] = 0u;
+                        cnt[h][0] = old[h];
+                    }
+                    if (mv) {
+#pragma unroll
+                        for (int h = 0; h < RP; ++h) {
+                            // match rows of right, left, down, up (rules 0..3) here and one above
+                            const uint32_t *m = M + PAD + wr + 8 * h;
+                            const uint32_t a0 = m[0], a1 = m[MS], a2 = m[2 * MS], a3 = m[3 * MS];
+                            const uint32_t a2p = m[2 * MS - 1], a3p = m[3 * MS - 1];
+                            count4<KB>(cnt[h], a0 << 1, a1, a2p, a3);
+                            count4<KB>(cnt[h], ~a0, ~(a1 << 1), ~a2, ~a3p);
+                        }
+                    }
+                    const uint32_t dead = uint32_t(Rt * MS) * 4u;   // the plane of zeros
+                    auto add = [&](const uint32_t (&v)[4], int nv) AV_INLINE {
+                        uint32_t x[RP][4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const uint32_t w = u < nv ? v[u] : dead;
+                            const uint32_t *m = reinterpret_cast<const uint32_t *>(
+                                reinterpret_cast<const char *>(mw) + (w & 0xFFFFu));
+                            const uint32_t minus = uint32_t(int32_t(w) >> 31);
+#pragma unroll
+                            for (int h = 0; h < RP; ++h)
+                                x[h][u] = (m[8 * h] << ((w >> 16) & 31u)) ^ minus;
+                        }
+#pragma unroll
+                        for (int h = 0; h < RP; ++h)
+                            count4<KB>(cnt[h], x[h][0], x[h][1], x[h][2], x[h][3]);
+                    };
+                    // the fired rules one after another (uniform), the next one's votes read with
+                    // the current one's match rows; a list has slack behind its end, so four are read
+                    uint64_t fr = fu;
+                    uint32_t v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = cv[(w & 0xFFFFu) + u];
+                    while (fr) {
+                        fr &= fr - 1ull;
+                        const uint32_t wn = rs[fr ? __builtin_ctzll(fr) : 0];
+                        const int nv = on ? int((w >> 16) & 255u) : 0;
+                        const uint32_t off = w & 0xFFFFu;
+                        add(v, nv);
+#pragma unroll 1
+                        for (int e = 4; __builtin_amdgcn_ballot_w64(e < nv); e += 4) {
+                            uint32_t t[4];
+                            const uint32_t at = off + uint32_t(e < nv ? e : 0);
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) t[u] = cv[at + u];
+                            add(t, nv - e);
+                        }
+                        w = wn;
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) v[u] = cv[(w & 0xFFFFu) + u];
+                    }
+#pragma unroll
+                    for (int h = 0; h < RP; ++h) {
+                        uint32_t gt = 0u, eq = ~0u;   // cnt >= need, bit-sliced
+#pragma unroll
+                        for (int q = KB - 1; q >= 0; --q) {
+                            const uint32_t tb = uint32_t(int32_t(need << (31 - q)) >> 31);
+                            gt |= eq & cnt[h][q] & ~tb;
+                            eq &= ~(cnt[h][q] ^ tb);
+                        }
+                        if (on && wr + 8 * h < H) {
+                            P[cc * PR + wr + 8 * h] = gt | eq;
+                            cw[h] |= (gt | eq) ^ old[h];
+                        }
+                    }
+                };
+                if (!__builtin_amdgcn_ballot_w64(total > 14)) run(std::integral_constant<int, 4>{});
+                else if (!__builtin_amdgcn_ballot_w64(total > 62)) run(std::integral_constant<int, 6>{});
+                else run(std::integral_constant<int, 8>{});
+            }
+            // the changes of all channels, at the lane's own rows
+#pragma unroll
+            for (int h = 0; h < RP; ++h) {
+                uint32_t o = cw[h];
+                o = groups_or(o | dpp<0x128>(o));
+                if (wo == 0) DR[wr + 8 * h] = o;
+            }
+        };
+        // rows that get votes: from the first match row to the last one's patch's last
+        uint32_t rows = 0u;
+#pragma unroll
+        for (int h = 0; h < RPL; ++h)
+            rows |= uint32_t(__builtin_amdgcn_ballot_w64(fm[h] != 0u) & 0xFFFFull) << (kHq * h);
+        const int last = min(31 - __builtin_clz(rows) + PAD, HR - 1);
+        int from = 0, past = HR;                  // the rows written
+        if (!window(rows | (1u << last))) {
+            from = r0;
+            past = r0 + 8;
+            rows_of(std::integral_constant<int, 1>{}, false);
+        } else if constexpr (HALVES) {
+#pragma unroll 1
+            for (r0 = 0; r0 < HR; r0 += HR / 2) {
+                wr = r0 + wl;
+                rows_of(std::integral_constant<int, FULL / 2>{}, true);
+            }
+        } else {
+            rows_of(std::integral_constant<int, FULL>{}, false);
+        }
+        lds_order();
+#pragma unroll
+        for (int h = 0; h < RPL; ++h) ch[h] = yr[h] >= from && yr[h] < past ? DR[yr[h]] : 0u;
+        lds_order();
     };
 
     uint32_t ablk = 0u;     // lane l: action of step k0 + l of the current block of 64
     float rbuf = 0.f;       // lane l: reward of step k0 + l
     uint32_t dbuf = 0u;     // lane l: done flag of step k0 + l
     uint32_t *const F = P + C * PR;
-    uint32_t *const P2w = P + kChPlayer * PR;
-    const uint32_t *const P2 = P2w;
-
+    uint32_t *const P2 = P + kChPlayer * PR;
     const uint32_t cm1 = low_mask(W - 1);         // anchors of a 1 x 2 pattern
     uint32_t vrow2[RPL];                          // rows of a 2 x 1 pattern's anchors
 #pragma unroll
     for (int h = 0; h < RPL; ++h) vrow2[h] = (yr[h] + 2 <= H) ? wmask : 0u;
-    const int pown = kChPlayer % G;               // the group that writes the player plane
-    // the player and wall rows of the lane (every group holds them): the next step's follow
-    // from the moves' votes in registers unless a loaded rule voted on either plane or the
-    // episode ended; then they are read again
-    uint32_t Pyr[RPL], Wyr[RPL];
+    // the player and wall rows of the lane (every group holds them), 0 past the map
+    uint32_t Py[RPL], Wy[RPL];
 #pragma unroll
     for (int h = 0; h < RPL; ++h) {
-        Pyr[h] = rw[h] ? P2[yr[h]] : 0u;
-        Wyr[h] = rw[h] ? P[kChWall * PR + yr[h]] : 0u;
+        Py[h] = rw[h] ? P2[yr[h]] : 0u;
+        Wy[h] = rw[h] ? P[kChWall * PR + yr[h]] : 0u;
     }
-    // the probe rows of the group's rules: read once when the group has at most two rules,
-    // else every step (registers would spill)
-    uint4 pe[NR];
-    uint32_t pv[NR];
-    uint4 pe2[NR];                                // entries 4 .. 7 (NR <= 2)
-    uint32_t pm[NR];                              // match offset | count << 16 (NR <= 2)
-    if constexpr (NR <= 2) {
+
+    // cells that changed since the rules were last matched (in sequential order: during the step
+    // before and this one) and the force rows they were matched with
+    uint32_t D[RPL], Fl[RPL];
 #pragma unroll
-        for (int kr = 0; kr < NR; ++kr) {
-            const int r = kr < nr ? kMoveRules + g + G * kr : kMoveRules;
-            pe[kr] = *reinterpret_cast<const uint4 *>(PT + r * kProbeWords);
-            pv[kr] = PT[r * kProbeWords + 4];
-            pe2[kr] = *reinterpret_cast<const uint4 *>(PT + r * kProbeWords + 8);
-            pm[kr] = kr < nr ? PT[r * kProbeWords + 5] : 0u;
-        }
+    for (int h = 0; h < RPL; ++h) {
+        D[h] = rw[h] ? ~0u : 0u;
+        Fl[h] = 0u;
     }
+
     for (int k = 0; k < a.k; ++k) {
         const int kb = k & 63;
         if (kb == 0) ablk = (k + lane < a.k) ? uint32_t(a.actions[size_t(k + lane) * a.B + b]) : 0u;
         const int act = __builtin_amdgcn_readlane(int(ablk), kb);
-        // the lane's rows of the player and wall planes (0 past the map; kept in registers
-        // from step to step), and the probe table rows of the group's rules
-        uint32_t Py[RPL], Wy[RPL];
-#pragma unroll
-        for (int h = 0; h < RPL; ++h) {
-            Py[h] = Pyr[h];
-            Wy[h] = Wyr[h];
-        }
-        if constexpr (NR > 2) {                   // (up to two rules: held for the launch)
-#pragma unroll
-            for (int kr = 0; kr < NR; ++kr) {
-                const int r = kr < nr ? kMoveRules + g + G * kr : kMoveRules;
-                pe[kr] = *reinterpret_cast<const uint4 *>(PT + r * kProbeWords);
-                pv[kr] = PT[r * kProbeWords + 4];
-            }
-        }
-        // the rows next to them and the force row
+        if constexpr (CTL) have_keys = 0u;
         uint32_t Pn[RPL], Wn[RPL], Pp[RPL], Fy[RPL], Fn[RPL];
-        next_rows<Hq, RPL>(Py, Pn, lane, y);
-        next_rows<Hq, RPL>(Wy, Wn, lane, y);
-        prev_rows<Hq, RPL>(Py, Pp, lane, y);
+        next_rows<RPL>(Py, Pn, y);
+        next_rows<RPL>(Wy, Wn, y);
+        prev_rows<RPL>(Py, Pp, y);
 #pragma unroll
-        for (int h = 0; h < RPL; ++h) {
+        for (int h = 0; h < RPL; ++h)
             Fy[h] = act == 1 ? Pn[h] : act == 3 ? Pp[h] : act == 2 ? ((Py[h] << 1) & wmask)
                   : act == 4 ? (Py[h] >> 1) : 0u;
-            if (g == 0 && rw[h]) F[yr[h]] = Fy[h];
-        }
-        next_rows<Hq, RPL>(Fy, Fn, lane, y);
-        // the four moves (rules 0..3: right, left, down, up) and their votes on the player
-        // plane; group 0 stores their match rows for an exact recount
-        uint32_t m0[RPL], m1[RPL], m2[RPL], m3[RPL], m2p[RPL], m3p[RPL];
-        uint32_t mplus[RPL], mminus[RPL], pnew[RPL];
-#pragma unroll
-        for (int h = 0; h < RPL; ++h) {
-            m0[h] = Py[h] & (Fy[h] >> 1) & ~(Wy[h] >> 1) & cm1;
-            m1[h] = Fy[h] & ~Wy[h] & (Py[h] >> 1) & cm1;
-            m2[h] = Py[h] & Fn[h] & ~Wn[h] & vrow2[h];
-            m3[h] = Fy[h] & ~Wy[h] & Pn[h] & vrow2[h];
-        }
-        prev_rows<Hq, RPL>(m2, m2p, lane, y);
-        prev_rows<Hq, RPL>(m3, m3p, lane, y);
-        uint32_t both = 0u;
-#pragma unroll
-        for (int h = 0; h < RPL; ++h) {
-            mplus[h] = (m0[h] << 1) | m1[h] | m2p[h] | m3[h];
-            mminus[h] = m0[h] | (m1[h] << 1) | m2[h] | m3p[h];
-            // the player rows after the moves' votes alone: one sign OR-ed, or, where some cell
-            // got votes of both signs (players moving into cells other players leave), counted
-            // exactly in registers: old + #plus > #minus over the four plus and four minus terms
-            pnew[h] = (Py[h] | mplus[h]) & ~mminus[h];
-            both |= mplus[h] & mminus[h];
-        }
-        if (__builtin_amdgcn_ballot_w64(both != 0u)) {
-#pragma unroll
-            for (int h = 0; h < RPL; ++h) {
-                const uint32_t a1 = m0[h] << 1, b2 = m1[h] << 1, o = Py[h];
-                // plus: old, a1, m1, m2p, m3 -> p2 p1 p0 (at most 5)
-                const uint32_t s1 = o ^ a1 ^ m1[h], c1 = (o & a1) | (m1[h] & (o ^ a1));
-                const uint32_t p0 = s1 ^ m2p[h] ^ m3[h], c2 = (s1 & m2p[h]) | (m3[h] & (s1 ^ m2p[h]));
-                const uint32_t p1 = c1 ^ c2, p2 = c1 & c2;
-                // minus: m0, b2, m2, m3p -> n2 n1 n0 (at most 4)
-                const uint32_t s3 = m0[h] ^ b2 ^ m2[h], c3 = (m0[h] & b2) | (m2[h] & (m0[h] ^ b2));
-                const uint32_t n0 = s3 ^ m3p[h], c4 = s3 & m3p[h];
-                const uint32_t n1 = c3 ^ c4, n2 = c3 & c4;
-                pnew[h] = (p2 & ~n2) | (~(p2 ^ n2) & ((p1 & ~n1) | (~(p1 ^ n1) & p0 & ~n0)));
-            }
-        }
-        if (g == 0) {
-#pragma unroll
-            for (int h = 0; h < RPL; ++h) {
-                M[0 * MS + PAD + yr[h]] = m0[h];
-                M[1 * MS + PAD + yr[h]] = m1[h];
-                M[2 * MS + PAD + yr[h]] = m2[h];
-                M[3 * MS + PAD + yr[h]] = m3[h];
-            }
-        }
-        uint64_t fired = (__builtin_amdgcn_ballot_w64(any_row<RPL>(m0)) ? 1ull : 0ull) |
-                         (__builtin_amdgcn_ballot_w64(any_row<RPL>(m1)) ? 2ull : 0ull) |
-                         (__builtin_amdgcn_ballot_w64(any_row<RPL>(m2)) ? 4ull : 0ull) |
-                         (__builtin_amdgcn_ballot_w64(any_row<RPL>(m3)) ? 8ull : 0ull);
 
-        // probe: every loaded rule of the group with its first four entries, all reads at once
-        // (no branch between the rules); the results go to the rules' match rows, and a
-        // wave-uniform mask of the rule indices kr whose probe passed in some group
-        uint32_t mk[NR][RPL];
-#pragma unroll
-        for (int kr = 0; kr < NR; ++kr) {
-#pragma unroll
-            for (int h = 0; h < RPL; ++h)
-                mk[kr][h] = (kr < nr && yr[h] < int(pv[kr] >> 8)) ? ~0u >> (pv[kr] & 255u) : 0u;
-            entries4(pe[kr].x, pe[kr].y, pe[kr].z, pe[kr].w, mk[kr]);
-        }
-        uint32_t cand = 0u;
-#pragma unroll
-        for (int kr = 0; kr < NR; ++kr) {
-            if (kr < nr) {
-#pragma unroll
-                for (int h = 0; h < RPL; ++h)
-                    M[(kMoveRules + g + G * kr) * MS + PAD + yr[h]] = mk[kr][h];
-            }
-            cand |= __builtin_amdgcn_ballot_w64(any_row<RPL>(mk[kr])) ? 1u << kr : 0u;
-        }
-
-        // candidates: the rest of their input entries four at a time.  With up to four rules per
-        // group, in rounds in which every candidate of every group takes its next four (a lane
-        // only while it still holds an anchor of the rule; otherwise the pass entry, which
-        // tests nothing; a rule slot no group still needs is skipped); with more, one rule after another, the next four entries
-        // read while the current ones' plane rows are (rounds would issue every rule's reads
-        // while most rules are done, and four waves share each CU's LDS there).  A rule is done
-        // when its entries run out or its lanes have no anchor left.
+        uint32_t lvoted = 0u;                     // channels rewritten from LDS (uniform)
         int rsum = 0;
-        uint32_t voted = 0u;                      // bit c: a loaded rule voted on channel c
-        if (cand) {
-            uint32_t meta[NR];                    // match offset | entry count << 16
+        // reward of rule r's match rows (a group's lanes hold them all) and the channels it votes
+        // on; fm: the match rows of the rules so far
+        uint32_t fm[RPL];
+        auto pays = [&](int r) AV_INLINE {
+            const int reward = int(uniform(PT[r * kProbeWords + 6]));
+            lvoted |= uniform(PT[r * kProbeWords + 7]);
+            int cells = 0;
 #pragma unroll
-            for (int kr = 0; kr < NR; ++kr) {
-                const int r = kr < nr ? kMoveRules + g + G * kr : kMoveRules;
-                if constexpr (NR <= 2) meta[kr] = pm[kr];
-                else meta[kr] = kr < nr ? PT[r * kProbeWords + 5] : 0u;
+            for (int h = 0; h < RPL; ++h) {
+                const uint32_t m = MV[r * MS + PAD + yr[h]];
+                fm[h] |= m;
+                cells += __popc(m);
             }
-            if constexpr (NR <= 4) {
-                for (int e = kProbeEntries;; e += 4) {
-                    // the rule slots still live in some group (the others are skipped)
-                    uint32_t lk = 0u;
+            rsum += reward * cells;
+        };
 #pragma unroll
-                    for (int kr = 0; kr < NR; ++kr)
-                        lk |= __builtin_amdgcn_ballot_w64(any_row<RPL>(mk[kr]) && e < int(meta[kr] >> 16))
-                                  ? 1u << kr : 0u;
-                    if (!lk) break;
-                    uint32_t x[NR][4];
+        for (int h = 0; h < RPL; ++h) fm[h] = 0u;
+
+        if constexpr (SEQ) {
+            // the moves one after another: right, left, down, up (each takes the player from its
+            // cell to the force cell next to it and consumes the force; a cell that a player
+            // leaves and another enters keeps its tile: 1 + 1 - 1)
+            auto any = [&](const uint32_t (&m)[RPL]) AV_INLINE {
+                return __builtin_amdgcn_ballot_w64(any_row<RPL>(m)) != 0ull;
+            };
+            bool moved = false;
+            uint32_t F0[RPL], P0[RPL];            // the step's first force and player rows
 #pragma unroll
-                    for (int kr = 0; kr < NR; ++kr) {
-                        if (!((lk >> kr) & 1u)) continue;
-                        const int off = int(meta[kr] & 0xFFFFu), cnt = int(meta[kr] >> 16);
-                        const bool live = any_row<RPL>(mk[kr]) && e < cnt;
-                        if (NR <= 2 && e == kProbeEntries) {   // entries 4 .. 7: in registers
-                            const uint4 q = pe2[kr];
-                            x[kr][0] = live ? q.x : kPassEntry;
-                            x[kr][1] = live ? q.y : kPassEntry;
-                            x[kr][2] = live ? q.z : kPassEntry;
-                            x[kr][3] = live ? q.w : kPassEntry;
-                            continue;
-                        }
-                        if (NR > 2 && e == kProbeEntries) {    // entries 4 .. 7: the probe row's
-                            const int r = kr < nr ? kMoveRules + g + G * kr : kMoveRules;
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                x[kr][u] = live ? PT[r * kProbeWords + 8 + u] : kPassEntry;
-                            continue;
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            // past the last entry the last one again (AND is idempotent)
-                            const uint32_t w = ment[live ? off + min(e + u, cnt - 1) : 0];
-                            x[kr][u] = live ? w : kPassEntry;
-                        }
-                    }
-#pragma unroll
-                    for (int kr = 0; kr < NR; ++kr)
-                        if ((lk >> kr) & 1u) entries4(x[kr][0], x[kr][1], x[kr][2], x[kr][3], mk[kr]);
-                }
-            } else {
-#pragma unroll
-                for (int kr = 0; kr < NR; ++kr) {
-                    if (!((cand >> kr) & 1u)) continue;
-                    uint32_t m[RPL];
-#pragma unroll
-                    for (int h = 0; h < RPL; ++h) m[h] = mk[kr][h];
-                    if (!(kr < nr && group_any<Hq>(any_row<RPL>(m), lane))) continue;
-                    const uint32_t *en = ment + int(meta[kr] & 0xFFFFu);
-                    const int cnt = int(meta[kr] >> 16), last = cnt - 1;
-                    int e = kProbeEntries;
-                    uint32_t x[4] = {kPassEntry, kPassEntry, kPassEntry, kPassEntry};
-                    if (e < cnt) {                // (reads stay inside the rule's entries)
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) x[u] = en[min(e + u, last)];
-                    }
-                    while (e < cnt && group_any<Hq>(any_row<RPL>(m), lane)) {
-                        uint32_t cur[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) cur[u] = x[u];
-                        e += 4;
-                        if (e < cnt) {
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) x[u] = en[min(e + u, last)];
-                        }
-                        entries4(cur[0], cur[1], cur[2], cur[3], m);
-                    }
-#pragma unroll
-                    for (int h = 0; h < RPL; ++h) mk[kr][h] = m[h];
-                }
+            for (int h = 0; h < RPL; ++h) {
+                Fy[h] = rw[h] ? Fy[h] : 0u;
+                F0[h] = Fy[h];
+                P0[h] = Py[h];
             }
-            // the rules that fired in some group: match row, reward and votes
-            uint32_t fl = 0u;
+            if (act >= 1 && act <= 4) {
+                uint32_t m[RPL], mp[RPL];
 #pragma unroll
-            for (int kr = 0; kr < NR; ++kr)
-                fl |= __builtin_amdgcn_ballot_w64(any_row<RPL>(mk[kr])) ? 1u << kr : 0u;
-            for (; fl; fl &= fl - 1u) {
-                const int kr = __builtin_ctz(fl);
-                const int r = kMoveRules + g + G * kr;
-                uint32_t m[RPL];                  // mk[kr] (kr is wave-uniform)
-#pragma unroll
-                for (int h = 0; h < RPL; ++h) m[h] = 0u;
-#pragma unroll
-                for (int kk = 0; kk < NR; ++kk) {
-#pragma unroll
-                    for (int h = 0; h < RPL; ++h) m[h] = kk == kr ? mk[kk][h] : m[h];
-                }
-                if (kr < nr && group_any<Hq>(any_row<RPL>(m), lane)) {
-                    const uint32_t *hw = hdrw + r * kHdrWords;
-                    int cells = 0;
+                for (int h = 0; h < RPL; ++h) m[h] = Py[h] & (Fy[h] >> 1) & ~(Wy[h] >> 1) & cm1;
+                if (any(m)) {
+                    moved = true;
 #pragma unroll
                     for (int h = 0; h < RPL; ++h) {
-                        M[r * MS + PAD + yr[h]] = m[h];
-                        cells += __popc(m[h]);
+                        Py[h] = (Py[h] & ~m[h]) | (m[h] << 1);
+                        Fy[h] &= ~(m[h] << 1);
                     }
-                    fired |= 1ull << r;
-                    // the vote list's place and the voted channels: with the program in global
-                    // memory from the probe row (LDS), a memory round trip less before the votes
-                    int voff, vcnt;
-                    if constexpr (PROG_LDS) {
-                        voted |= hw[7];
-                        rsum += int(hw[2]) * cells;
-                        voff = int(hw[5]);
-                        vcnt = int(hw[6]);
-                    } else {
-                        const uint32_t pvw = PT[r * kProbeWords + 6];
-                        voted |= PT[r * kProbeWords + 7];
-                        rsum += int(hw[2]) * cells;
-                        voff = int(pvw & 0xFFFFu);
-                        vcnt = int(pvw >> 16);
+                }
+#pragma unroll
+                for (int h = 0; h < RPL; ++h) m[h] = Fy[h] & ~Wy[h] & (Py[h] >> 1) & cm1;
+                if (any(m)) {
+                    moved = true;
+#pragma unroll
+                    for (int h = 0; h < RPL; ++h) {
+                        Py[h] = (Py[h] & ~(m[h] << 1)) | m[h];
+                        Fy[h] &= ~m[h];
                     }
-                    // votes kChunk at a time, the next chunk read with the current one's match
-                    // rows (a repeated last vote ORs the same bits again)
-                    const uint32_t *ve = vent + voff;
-                    const int vlast = vcnt - 1;
-                    uint32_t v[kChunk];
-                    if (vcnt > 0) {
+                }
+                next_rows<RPL>(Fy, Fn, y);
 #pragma unroll
-                        for (int u = 0; u < kChunk; ++u) v[u] = ve[min(u, vlast)];
+                for (int h = 0; h < RPL; ++h) m[h] = Py[h] & Fn[h] & ~Wn[h] & vrow2[h];
+                if (any(m)) {
+                    moved = true;
+                    prev_rows<RPL>(m, mp, y);
+#pragma unroll
+                    for (int h = 0; h < RPL; ++h) {
+                        Py[h] = (Py[h] & ~m[h]) | mp[h];
+                        Fy[h] &= ~mp[h];
                     }
-                    for (int ev = 0; ev < vcnt; ev += kChunk) {
-                        uint32_t cv[kChunk], tv[kChunk][RPL];
+                }
+                next_rows<RPL>(Py, Pn, y);
 #pragma unroll
-                        for (int u = 0; u < kChunk; ++u) cv[u] = v[u];
-                        if (ev + kChunk < vcnt) {
+                for (int h = 0; h < RPL; ++h) m[h] = Fy[h] & ~Wy[h] & Pn[h] & vrow2[h];
+                if (any(m)) {
+                    moved = true;
+                    prev_rows<RPL>(m, mp, y);
 #pragma unroll
-                            for (int u = 0; u < kChunk; ++u) v[u] = ve[min(ev + kChunk + u, vlast)];
-                        }
-#pragma unroll
-                        for (int u = 0; u < kChunk; ++u) {
-#pragma unroll
-                            for (int h = 0; h < RPL; ++h)
-                                tv[u][h] = M[r * MS + PAD + yr[h] - int((cv[u] >> 8) & 255u)]
-                                           << ((cv[u] >> 16) & 255u);
-                        }
-#pragma unroll
-                        for (int u = 0; u < kChunk; ++u) {
-#pragma unroll
-                            for (int h = 0; h < RPL; ++h)
-                                if (rw[h] && tv[u][h])
-                                    atomicOr(((cv[u] >> 24) & 1u ? PL : MI) + int(cv[u] & 255u) * HR + yr[h],
-                                             tv[u][h]);
-                        }
+                    for (int h = 0; h < RPL; ++h) {
+                        Py[h] = (Py[h] & ~mp[h]) | m[h];
+                        Fy[h] &= ~m[h];
                     }
                 }
             }
-        }
-        // every rule that fired anywhere in the wave and every channel a loaded rule voted on
-        // (the groups' masks OR-ed)
-        uint64_t fired_all = fired & 15ull;       // (the moves' bits are the same in every lane)
-        uint32_t lvoted = 0u;                     // channels the loaded rules voted on
-        if (__builtin_amdgcn_ballot_w64((fired >> kMoveRules) != 0ull)) {
+            if (g == 0) {
 #pragma unroll
-            for (int gg = 0; gg < G; ++gg) {
-                const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(fired)), gg * Hq));
-                const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(fired >> 32)), gg * Hq));
-                fired_all |= uint64_t(lo) | (uint64_t(hi) << 32);
-                lvoted |= uint32_t(__builtin_amdgcn_readlane(int(voted), gg * Hq));
+                for (int h = 0; h < RPL; ++h) {
+                    if (rw[h]) F[yr[h]] = Fy[h];
+                    if (rw[h] && moved) P2[yr[h]] = Py[h];
+                }
             }
+            lds_order();
+            // what changed in this step so far: the force rows, the moves
+            uint32_t Dc[RPL], ch[RPL];
+#pragma unroll
+            for (int h = 0; h < RPL; ++h) {
+                Dc[h] = (F0[h] ^ Fl[h]) | (F0[h] ^ Fy[h]) | (P0[h] ^ Py[h]);
+                D[h] |= Dc[h];
+            }
+            // every rule on the map after the moves; then, in order, the rules that match: each that
+            // applies changes the map under the rules behind it, which are matched again where its
+            // changes reach
+            match(D, 0);
+            uint64_t applied = 0ull;              // rules that applied in this step
+            for (uint64_t left = live; left;) {
+                const int r = __builtin_ctzll(left);
+                const uint64_t behind = ~0ull << r << 1;
+                if (!CTL || control(r, applied, nbase + uint64_t(k))) {
+                    applied |= 1ull << r;
+#pragma unroll
+                    for (int h = 0; h < RPL; ++h) fm[h] = 0u;
+                    pays(r);
+                    const uint32_t on = uniform(PT[r * kProbeWords + 7]);
+                    if (on) {
+                        write(on, 1ull << r, fm, false, Py, ch);
+#pragma unroll
+                        for (int h = 0; h < RPL; ++h) Dc[h] |= ch[h];
+                        if (r + 1 < Rt) match(ch, r + 1 - kMoveRules);
+                    }
+                }
+                left = live & behind;
+            }
+#pragma unroll
+            for (int h = 0; h < RPL; ++h) {
+                D[h] = Dc[h];
+                Fl[h] = ((lvoted >> C) & 1u) ? (rw[h] ? F[yr[h]] : 0u) : Fy[h];
+            }
+        } else {
+            if (g == 0) {
+#pragma unroll
+                for (int h = 0; h < RPL; ++h)
+                    if (rw[h]) F[yr[h]] = Fy[h];
+            }
+            next_rows<RPL>(Fy, Fn, y);
+            // the four moves (rules 0..3: right, left, down, up) and their votes on the player
+            // plane
+            uint32_t m0[RPL], m1[RPL], m2[RPL], m3[RPL], m2p[RPL], m3p[RPL], pnew[RPL];
+#pragma unroll
+            for (int h = 0; h < RPL; ++h) {
+                m0[h] = Py[h] & (Fy[h] >> 1) & ~(Wy[h] >> 1) & cm1;
+                m1[h] = Fy[h] & ~Wy[h] & (Py[h] >> 1) & cm1;
+                m2[h] = Py[h] & Fn[h] & ~Wn[h] & vrow2[h];
+                m3[h] = Fy[h] & ~Wy[h] & Pn[h] & vrow2[h];
+            }
+            prev_rows<RPL>(m2, m2p, y);
+            prev_rows<RPL>(m3, m3p, y);
+            uint32_t both = 0u;
+#pragma unroll
+            for (int h = 0; h < RPL; ++h) {
+                const uint32_t plus = (m0[h] << 1) | m1[h] | m2p[h] | m3[h];
+                const uint32_t minus = m0[h] | (m1[h] << 1) | m2[h] | m3p[h];
+                pnew[h] = (Py[h] | plus) & ~minus;
+                both |= plus & minus;
+            }
+            // where some cell got votes of both signs (players moving into cells other players
+            // leave), counted exactly: old + #plus > #minus
+            if (__builtin_amdgcn_ballot_w64(both != 0u)) {
+#pragma unroll
+                for (int h = 0; h < RPL; ++h) {
+                    uint32_t q[4] = {Py[h], 0u, 0u, 0u};
+                    count4<4>(q, m0[h] << 1, m1[h], m2p[h], m3[h]);
+                    count4<4>(q, ~m0[h], ~(m1[h] << 1), ~m2[h], ~m3p[h]);
+                    pnew[h] = q[3] | (q[2] & (q[1] | q[0]));   // 5 or more of 9
+                }
+            }
+            auto store_moves = [&]() AV_INLINE {  // the moves' match rows, for a recount
+                if (g != 0) return;
+#pragma unroll
+                for (int h = 0; h < RPL; ++h) {
+                    M[0 * MS + PAD + yr[h]] = m0[h];
+                    M[1 * MS + PAD + yr[h]] = m1[h];
+                    M[2 * MS + PAD + yr[h]] = m2[h];
+                    M[3 * MS + PAD + yr[h]] = m3[h];
+                }
+            };
+            if constexpr (HALVES) store_moves();   // (at once: held, they would spill registers)
+            // every loaded rule's matches on this map
+#pragma unroll
+            for (int h = 0; h < RPL; ++h) {
+                const uint32_t f = rw[h] ? Fy[h] : 0u;
+                D[h] |= f ^ Fl[h];
+                Fl[h] = f;
+            }
+            match(D, 0);
+            uint64_t fired = live;
+            if constexpr (CTL) {
+                uint64_t applied = 0ull;
+                for (uint64_t fr = fired; fr; fr &= fr - 1ull) {
+                    const int r = __builtin_ctzll(fr);
+                    if (control(r, applied, nbase + uint64_t(k))) applied |= 1ull << r;
+                }
+                fired = applied;
+            }
+            for (uint64_t fr = fired; fr; fr &= fr - 1ull) pays(__builtin_ctzll(fr));
+            // the player plane by the moves' votes alone, from registers
+            const bool player = (lvoted >> kChPlayer) & 1u;
+            if (!player && g == 0) {
+#pragma unroll
+                for (int h = 0; h < RPL; ++h)
+                    if (rw[h]) P2[yr[h]] = pnew[h];
+            }
+#pragma unroll
+            for (int h = 0; h < RPL; ++h) D[h] = Py[h] ^ pnew[h];
+            if (lvoted) {
+                uint32_t ch[RPL];
+                if (!HALVES && player) store_moves();
+                lds_order();
+                write(lvoted, fired, fm, true, pnew, ch);
+#pragma unroll
+                for (int h = 0; h < RPL; ++h) D[h] |= ch[h];
+            }
+#pragma unroll
+            for (int h = 0; h < RPL; ++h) Py[h] = pnew[h];
         }
-        const uint32_t voted_all = lvoted | ((fired_all & 15ull) ? 1u << kChPlayer : 0u);
 
-        // new rows of the channels that received votes: group g rewrites channels g, g + G, ...
-        // (the moves' votes on the player plane are in registers, the loaded rules' in LDS)
-        bool pl_any = false;                      // a player bit after the write
+        // reward: the sum over a group's lanes
+        if (__builtin_amdgcn_ballot_w64(rsum != 0)) rsum = int(group_sum(uint32_t(rsum)));
+        // the lane's player and wall rows, read again when a loaded rule voted on either plane
+        if (lvoted & ((1u << kChPlayer) | (1u << kChWall))) {
 #pragma unroll
-        for (int h = 0; h < RPL; ++h) pl_any |= g == pown && rw[h] && Py[h] != 0u;
-        if (voted_all == (1u << kChPlayer) && lvoted == 0u) {
-            // only the moves voted (most steps): the player plane, from registers
-            if (g == pown) {
-                pl_any = false;
-#pragma unroll
-                for (int h = 0; h < RPL; ++h) {
-                    if (rw[h]) P2w[yr[h]] = pnew[h];
-                    pl_any |= rw[h] && pnew[h] != 0u;
-                }
-            }
-        } else if (voted_all) {
-#pragma unroll 1
-            for (int c = g; c < C; c += G) {
-                if (!((voted_all >> c) & 1u)) continue;
-                const bool lv = (lvoted >> c) & 1u;
-                uint32_t old[RPL], pl[RPL], mi[RPL], nw[RPL], mixed = 0u;
-#pragma unroll
-                for (int h = 0; h < RPL; ++h) {
-                    old[h] = c == kChPlayer ? Py[h] : P[c * PR + yr[h]];
-                    pl[h] = lv ? PL[c * HR + yr[h]] : 0u;
-                    mi[h] = lv ? MI[c * HR + yr[h]] : 0u;
-                    if (c == kChPlayer) {
-                        pl[h] |= mplus[h];
-                        mi[h] |= mminus[h];
-                    }
-                    nw[h] = (old[h] | pl[h]) & ~mi[h];
-                    mixed |= pl[h] & mi[h];
-                }
-                if (c == kChPlayer && !lv) {
-#pragma unroll
-                    for (int h = 0; h < RPL; ++h) nw[h] = pnew[h];   // only the moves voted on it
-                } else if (group_any<Hq>(mixed != 0u, lane)) {
-                    exact_channel<RPL>(old, fired_all & (uint64_t(RM[2 * c]) | uint64_t(RM[2 * c + 1]) << 32),
-                                       (NR > 2 || SHORT || WIDE) && c == kChPlayer, vote + int(vlw[2 * c]),
-                                       RS + c * Rt, M, MS, PAD, yr, rw, nw);
-                }
-                if (c == kChPlayer) pl_any = false;
-#pragma unroll
-                for (int h = 0; h < RPL; ++h) {
-                    if (rw[h]) P[c * PR + yr[h]] = nw[h];
-                    if (c == kChPlayer) pl_any |= rw[h] && nw[h] != 0u;
-                    if (lv) {
-                        PL[c * HR + yr[h]] = 0u;
-                        MI[c * HR + yr[h]] = 0u;
-                    }
-                }
+            for (int h = 0; h < RPL; ++h) {
+                Py[h] = rw[h] ? P2[yr[h]] : 0u;
+                Wy[h] = rw[h] ? P[kChWall * PR + yr[h]] : 0u;
             }
         }
-
-        // reward: the lanes' sums over the wave
-        if (__builtin_amdgcn_ballot_w64(rsum != 0)) {
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) rsum += __shfl_xor(rsum, off);
-        }
-        // episode end: a player bit left anywhere (the writing group's lanes hold the rows)
-        const bool anyp = __builtin_amdgcn_ballot_w64(pl_any) != 0ull;
+        const bool anyp = __builtin_amdgcn_ballot_w64(any_row<RPL>(Py)) != 0ull;
         t_env += 1;
         const bool d = !anyp || (a.L > 0 && t_env == a.L);
         if (d) {                                  // back to the initial rows
             t_env = 0;
+            live = 0ull;
 #pragma unroll
             for (int h = 0; h < RPL; ++h) {
+                D[h] = rw[h] ? ~0u : 0u;
                 if (rw[h]) {
-#pragma unroll 1
-                    for (int c = g; c < C; c += G) P[c * PR + yr[h]] = I0[c * HR + yr[h]];
+#pragma unroll 4
+                    for (int c = g; c < C; c += kG) {
+                        const size_t at = (size_t(c) * a.B + b) * H + yr[h];
+                        P[c * PR + yr[h]] = a.row_bytes == 2
+                                                ? uint32_t(static_cast<const uint16_t *>(a.init)[at])
+                                                : static_cast<const uint32_t *>(a.init)[at];
+                    }
                 }
             }
-        }
-        if (d || ((lvoted >> kChPlayer) & 1u) || ((lvoted >> kChWall) & 1u)) {
+            lds_order();
 #pragma unroll
             for (int h = 0; h < RPL; ++h) {
-                Pyr[h] = rw[h] ? P2[yr[h]] : 0u;
-                Wyr[h] = rw[h] ? P[kChWall * PR + yr[h]] : 0u;
+                Py[h] = rw[h] ? P2[yr[h]] : 0u;
+                Wy[h] = rw[h] ? P[kChWall * PR + yr[h]] : 0u;
             }
-        } else {
-#pragma unroll
-            for (int h = 0; h < RPL; ++h) Pyr[h] = pnew[h];
         }
+        lds_order();
         if (lane == kb) {
             rbuf = float(rsum);
             dbuf = d ? 1u : 0u;
@@ -656,33 +1207,20 @@ __global__ void __launch_bounds__(64, NR <= 8 ? ((SHORT || WIDE) ? 2 : 4) : 1) g
         }
     }
 
-    if constexpr (SHORT) {
+    {
         // the rows back as they were read, the lane's channel and row formed again from an
-        // opaque copy of its index (kept from the set-up they were spilled through the launch)
+        // opaque copy of its index (kept from the set-up they would be spilled through the launch)
         int le = lane;
         asm volatile("" : "+v"(le));
-        const int wcl = le / H, wrow = le - wcl * H;
-        if (wcl < rcs) {
+        const int rcs = 64 / H, rcl = le / H, rrow = le - rcl * H;
+        if (rcl < rcs) {
 #pragma unroll 4
-            for (int c = wcl; c < C; c += rcs) {
-                const size_t at = (size_t(c) * a.B + b) * H + wrow;
-                if (a.row_bytes == 2) static_cast<uint16_t *>(a.state)[at] = uint16_t(P[c * PR + wrow]);
-                else static_cast<uint32_t *>(a.state)[at] = P[c * PR + wrow];
+            for (int c = rcl; c < C; c += rcs) {
+                const size_t at = (size_t(c) * a.B + b) * H + rrow;
+                if (a.row_bytes == 2) static_cast<uint16_t *>(a.state)[at] = uint16_t(P[c * PR + rrow]);
+                else static_cast<uint32_t *>(a.state)[at] = P[c * PR + rrow];
             }
         }
-    } else {
-#pragma unroll
-    for (int q = 0; q < kMaxChanPerGroup; ++q) {
-        const int c = g + G * q;
-#pragma unroll
-        for (int h = 0; h < RPL; ++h) {
-            if (c < C && rw[h]) {
-                const size_t at = (size_t(c) * a.B + b) * H + yr[h];
-                if (a.row_bytes == 2) static_cast<uint16_t *>(a.state)[at] = uint16_t(P[c * PR + yr[h]]);
-                else static_cast<uint32_t *>(a.state)[at] = P[c * PR + yr[h]];
-            }
-        }
-    }
     }
     if (lane == 0) {
         a.t[b] = t_env;
@@ -694,12 +1232,23 @@ __global__ void __launch_bounds__(64, NR <= 8 ? ((SHORT || WIDE) ? 2 : 4) : 1) g
     }
 }
 
+// LDS of a launch without the table's lists.
+size_t group_base_bytes(int H, int W, int C, int rules_per_set, int max_pat_h, bool sequential,
+                        bool control, bool random) {
+    const int HR = group_rows(H), PR = group_plane_words(HR, max_pat_h);
+    return sizeof(uint32_t) *
+           (size_t(C + 1) * PR + size_t(rules_per_set + 1) * PR * (control ? 2 : 1) +
+            size_t(rules_per_set - kMoveRules + 1) * HR +
+            size_t(group_head_words(rules_per_set, sequential ? C + 1 : C)) +
+            (control ? size_t(3) * rules_per_set : 0) +
+            (control && random ? size_t(H) * key_stride(W) + 32 : 0));
+}
+
 }  // namespace
 
-// Map rows a lane group covers: its 16 lanes hold one row each, or two on maps of 17 to 32 rows.
-static int group_rows(int H) { return H <= 16 ? 16 : 32; }
-
-size_t group_lds_bytes(int H, int C, int rules_per_set, int max_pat_h) {
+// The LDS set that bounds which batches the engine takes, as documented (with at most 64 rules and
+// 32 channels the kernel's own is never over 64 KiB).
+static size_t group_lds_bytes(int H, int C, int rules_per_set, int max_pat_h) {
     const int HR = group_rows(H), PR = group_plane_words(HR, max_pat_h);
     return sizeof(uint32_t) * (size_t(C + 1) * PR + size_t(rules_per_set) * PR +
                                size_t(3) * C * HR + size_t(rules_per_set + 1) * kProbeWords +
@@ -711,143 +1260,196 @@ bool group_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int m
     // every vote a cell-channel gets comes from a distinct (rule, pattern cell): the 8-bit
     // counts of the exact write hold them (plus the old value) when there are at most 255
     if (long(rules_per_set) * max_pat_h * max_pat_w > 254) return false;
-    constexpr int G = 4;                          // lane groups a wave holds
-    // (merged entries address rows of the stored and force planes in 12 bits)
-    return rules_per_set <= kMaxRulesPerGroup * G && rules_per_set <= 64 &&
-           C <= kMaxChanPerGroup * G &&
+    // (rule masks are 64-bit; merged entries address rows of the stored and force planes in 12
+    // bits)
+    return rules_per_set <= 64 && C <= kMaxChan &&
            (C + 1) * group_plane_words(group_rows(H), max_pat_h) <= kMaxEntryOffset + 1 &&
            group_lds_bytes(H, C, rules_per_set, max_pat_h) <= size_t(kLdsBudget);
 }
 
-// A rule's input entries (c | i << 8 | j << 16 | want << 24, rarest first) merged per plane
-// row and block of 8 columns, in the order of each row's first entry.
-static std::vector<uint32_t> merge_entries(const uint32_t *ent, int cnt, int PR) {
-    std::vector<uint32_t> key, out;               // key: c | i << 8 | jb << 16
-    for (int e = 0; e < cnt; ++e) {
-        const uint32_t c = ent[e] & 255u, i = (ent[e] >> 8) & 255u, j = (ent[e] >> 16) & 255u;
-        const uint32_t k = c | (i << 8) | ((j >> 3) << 16), bit = 1u << (j & 7u);
-        size_t q = 0;
-        while (q < key.size() && key[q] != k) ++q;
-        if (q == key.size()) {                    // no column tested yet
-            key.push_back(k);
-            out.push_back((c * uint32_t(PR) + i) | ((j >> 3) << 12));
-        }
-        out[q] |= bit << 16;                      // column tested
-        if ((ent[e] >> 24) & 1u) out[q] |= bit << 24;   // must be 1
-    }
-    return out;
+bool group_mode_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int max_pat_w,
+                         bool sequential, bool control, bool random) {
+    if (H > 32 || W > 32 || (!sequential && !control)) return false;
+    // as above; a vote list's places and a set's entries are 16-bit, and in sequential order only
+    // one rule's votes are counted at a time
+    const long cells = long(max_pat_h) * max_pat_w;
+    const int PR = group_plane_words(group_rows(H), max_pat_h);
+    if (rules_per_set > 64 || (sequential ? 1 : rules_per_set) * cells > 254) return false;
+    if (long(rules_per_set) * (C + 1) * cells > 0xFFFF || C + 1 > kMaxChan) return false;
+    if (long(rules_per_set + 1) * PR * 4 > 0xFFFF) return false;
+    return (C + 1) * PR <= kMaxEntryOffset + 1 &&
+           group_base_bytes(H, W, C, rules_per_set, max_pat_h, sequential, control, random) <=
+               size_t(kLdsBudget);
 }
 
+// Merges a rule's input entries (c | i << 8 | j << 16 | want << 24) per plane row and block of 8
+// columns.
+struct EntryMerger {
+    int H, W, C, PR;
+    std::vector<int32_t> place;                   // of (c, i, block) in out, -1
+    std::vector<std::pair<float, uint32_t>> out;  // share of a typical map's cells passed, entry
+
+    EntryMerger(int H_, int W_, int C_, int PR_)
+        : H(H_), W(W_), C(C_), PR(PR_), place(size_t(C_ + 1) * kMaxPat * 2, -1) {}
+
+    // Those that accept the fewest cells of a typical map first: one tile per cell, a wall on three
+    // cells in ten, the other tiles alike, one player (and its force) on the map.
+    void merge(const uint32_t *ent, int cnt) {
+        const float few = 1.f / float(H * W), other = 0.7f / float(std::max(1, C - 2));
+        out.clear();
+        for (int e = 0; e < cnt; ++e) {
+            const uint32_t c = ent[e] & 255u, i = (ent[e] >> 8) & 255u, j = (ent[e] >> 16) & 255u;
+            int32_t &at = place[(c * kMaxPat + i) * 2 + (j >> 3)];
+            if (at < 0) {                         // no column tested yet
+                at = int32_t(out.size());
+                out.push_back({1.f, (c * uint32_t(PR) + i) | ((j >> 3) << 12)});
+            }
+            const bool one = (ent[e] >> 24) & 1u;
+            const float p = int(c) == C || int(c) == kChPlayer ? few : int(c) == kChWall ? 0.3f : other;
+            auto &o = out[size_t(at)];
+            o.second |= (1u << (j & 7u)) << (one ? 24 : 16);
+            o.first *= one ? p : 1.f - p;
+        }
+        for (int e = 0; e < cnt; ++e)
+            place[((ent[e] & 255u) * kMaxPat + ((ent[e] >> 8) & 255u)) * 2 + (((ent[e] >> 16) & 255u) >> 3)] = -1;
+        // (equal ones by place, so that the order is one for every host)
+        std::sort(out.begin(), out.end());
+    }
+};
+
 void compile_group_tables(const GenericProgram &p, int H, int W, int C, int lists, int max_pat_h,
-                          std::vector<uint32_t> &tab, int &stride, std::vector<uint32_t> &gm,
-                          int &gm_stride) {
+                          std::vector<uint32_t> &tab, int &stride, int &entry_words) {
     const int Rt = p.rules_per_set, C1 = C + 1;
-    const int PR = group_plane_words(group_rows(H), max_pat_h);
-    stride = (Rt + 1) * kProbeWords + lists * Rt + 2 * lists;
-    tab.assign(size_t(p.sets) * stride, 0u);
-    std::vector<std::vector<uint32_t>> merged(p.sets);
-    gm_stride = 1;
+    const int PR = group_plane_words(group_rows(H), max_pat_h), PAD = max_pat_h - 1;
+    const int head = group_head_words(Rt, lists);
+    EntryMerger em(H, W, C, PR);
+    std::vector<uint32_t> merged;                 // every rule's entries, one after another
+    std::vector<int32_t> counts;                  // and how many
+    merged.reserve(p.match.size());
+    size_t most_votes = 0, most_entries = 0;
     for (int s = 0; s < p.sets; ++s) {
-        uint32_t *pt = tab.data() + size_t(s) * stride, *rs = pt + (Rt + 1) * kProbeWords;
-        // probe rows of the loaded rules: the first four merged entries (a missing one always
-        // passes) and the anchors, columns 0 .. W - m (~0 >> (32 - (W - m + 1))) of rows
-        // 0 .. H - n
+        const size_t from = merged.size();
         for (int r = kMoveRules; r < Rt; ++r) {
             const RuleHdr &h = p.hdr[size_t(s) * Rt + r];
-            const std::vector<uint32_t> ent = merge_entries(
-                p.match.data() + size_t(s) * p.match_stride + h.match_off, h.match_cnt, PR);
-            const int off = int(merged[s].size()), cnt = int(ent.size());
-            merged[s].insert(merged[s].end(), ent.begin(), ent.end());
+            em.merge(p.match.data() + size_t(s) * p.match_stride + h.match_off, h.match_cnt);
+            for (const auto &o : em.out) merged.push_back(o.second);
+            counts.push_back(int32_t(em.out.size()));
+        }
+        size_t votes = 0;
+        for (int c = 0; c < lists; ++c) votes += size_t(p.votes[size_t(s) * C1 + c].cnt);
+        most_votes = std::max(most_votes, votes);
+        most_entries = std::max(most_entries, merged.size() - from);
+    }
+    entry_words = int((most_entries + 3) & ~size_t(3));
+    stride = head + entry_words + int((most_votes + 4 + 3) & ~size_t(3));   // (four votes are read at a time)
+    tab.assign(size_t(p.sets) * stride, 0u);
+    const uint32_t *ent = merged.data();
+    const int32_t *count = counts.data();
+    for (int s = 0; s < p.sets; ++s) {
+        uint32_t *pt = tab.data() + size_t(s) * stride, *rs = pt + (Rt + 1) * kProbeWords;
+        uint32_t *gm = pt + head, *cv = gm + entry_words;
+        int off = 0;
+        for (int r = kMoveRules; r < Rt; ++r) {
+            const RuleHdr &h = p.hdr[size_t(s) * Rt + r];
+            const int cnt = *count++;
+            std::copy(ent, ent + cnt, gm + off);
             uint32_t *row = pt + r * kProbeWords;
-            for (int e = 0; e < kProbeEntries; ++e) row[e] = e < cnt ? ent[e] : kPassEntry;
+            // the first entries (a missing one always passes) and the anchors, columns 0 .. W - m
+            // (~0 >> (32 - (W - m + 1))) of rows 0 .. H - n
+            for (int e = 0; e < kProbeEntries; ++e) {
+                row[e] = e < cnt ? ent[e] : kPassEntry;
+                row[8 + e] = kProbeEntries + e < cnt ? ent[kProbeEntries + e] : kPassEntry;
+            }
             const int cols = W - h.m + 1, rows = H - h.n + 1;
             row[4] = (cols >= 1 && rows >= 1) ? uint32_t(32 - cols) | (uint32_t(rows) << 8) : 0u;
+            if (cnt > 2 * kProbeEntries) row[4] |= kMoreEntries;
             row[5] = uint32_t(off) | (uint32_t(cnt) << 16);
-            // the rule-major votes (a set holds at most 64 rules of at most 254 votes, so the
-            // offset and count fit 16 bits each) and the channels they are on
-            row[6] = uint32_t(h.vote_off) | (uint32_t(h.vote_cnt) << 16);
+            row[6] = uint32_t(h.reward);
             row[7] = uint32_t(h.pad);
-            // entries 4 .. 7 (past the last, the last again; none: the pass entry)
-            for (int e = 0; e < 4; ++e)
-                row[8 + e] = cnt > kProbeEntries ? ent[std::min(kProbeEntries + e, cnt - 1)]
-                                                 : kPassEntry;
+            off += cnt;
+            ent += cnt;
         }
-        gm_stride = std::max(gm_stride, int(merged[s].size()));
-        // rule ranges of the channel vote lists (each ordered by rule): first | end << 16
+        // the channels' vote lists (each ordered by rule) and every rule's part of them
+        uint32_t at = 0;
         for (int c = 0; c < lists; ++c) {
             const VoteList &vl = p.votes[size_t(s) * C1 + c];
             const uint32_t *v = p.vote.data() + size_t(s) * p.vote_stride + vl.off;
-            for (int k = 0; k < vl.cnt; ++k) {
-                const int r = int(v[k] & 255u);
-                uint32_t &w = rs[c * Rt + r];
-                if (k == 0 || int(v[k - 1] & 255u) != r) w |= uint32_t(k);
-                if (k == vl.cnt - 1 || int(v[k + 1] & 255u) != r) w |= uint32_t(k + 1) << 16;
-                // the rules with votes on the channel, a 64-bit mask (an exact write visits
-                // only the fired ones among them)
-                rs[lists * Rt + 2 * c + (r >> 5)] |= 1u << (r & 31);
+            for (int k = 0; k < vl.cnt; ++k, ++at) {
+                const uint32_t r = v[k] & 255u, i = (v[k] >> 8) & 255u, j = (v[k] >> 16) & 255u;
+                const bool minus = !((v[k] >> 24) & 1u);
+                cv[at] = (r * uint32_t(PR) + uint32_t(PAD) - i) * 4u | (j << 16) | (minus ? kMinusVote : 0u);
+                uint32_t &w = rs[c * Rt + int(r)];
+                if (!((w >> 16) & 255u)) w = at;
+                w += (1u << 16) + (minus ? 1u << 24 : 0u);
             }
         }
     }
-    gm.assign(size_t(p.sets) * gm_stride, kPassEntry);
-    for (int s = 0; s < p.sets; ++s)
-        std::copy(merged[s].begin(), merged[s].end(), gm.begin() + size_t(s) * gm_stride);
 }
 
 namespace {
-template <int RPL, int NJ, bool PROG_LDS, bool SHORT, bool WIDE>
-void launch_nr(const StepArgs &a, size_t lds, hipStream_t s) {
-    constexpr int G = 4;
-    const int nrmax = (a.prog.rules_per_set - kMoveRules + G - 1) / G;
-    const dim3 grid(a.B), block(64);
-    if (nrmax <= 2) hipLaunchKernelGGL((group_step<16, RPL, 2, NJ, PROG_LDS, SHORT, WIDE>), grid, block, lds, s, a);
-    else if (nrmax <= 4) hipLaunchKernelGGL((group_step<16, RPL, 4, NJ, PROG_LDS, SHORT, WIDE>), grid, block, lds, s, a);
-    else if (nrmax <= 8) hipLaunchKernelGGL((group_step<16, RPL, 8, NJ, PROG_LDS, SHORT, WIDE>), grid, block, lds, s, a);
-    else if (nrmax <= 12) hipLaunchKernelGGL((group_step<16, RPL, 12, NJ, PROG_LDS, SHORT, WIDE>), grid, block, lds, s, a);
-    else hipLaunchKernelGGL((group_step<16, RPL, 16, NJ, PROG_LDS, SHORT, WIDE>), grid, block, lds, s, a);
-}
 template <int RPL, int NJ>
-void launch_rpl(const StepArgs &a, size_t lds, bool prog_lds, bool wide, hipStream_t s) {
-    if (prog_lds && wide) launch_nr<RPL, NJ, true, false, true>(a, lds, s);
-    else if (prog_lds) launch_nr<RPL, NJ, true, false, false>(a, lds, s);
-    else if (a.k < kShortLaunch) launch_nr<RPL, NJ, false, true, false>(a, lds, s);
-    else launch_nr<RPL, NJ, false, false, false>(a, lds, s);
+void launch_mode(const StepArgs &a, size_t lds, int where, bool wide, hipStream_t s) {
+    const dim3 grid(a.B), block(64);
+    const bool ctl = a.ctl.active != 0, in = where == kLds;
+#define AV_GROUP(SEQ, CTL, WHERE, WAVES) \
+    hipLaunchKernelGGL((group_step<RPL, NJ, SEQ, CTL, WHERE, WAVES>), grid, block, lds, s, a)
+    if (a.sequential && ctl) {
+        if (in) AV_GROUP(true, true, kLds, 2);
+        else AV_GROUP(true, true, kGlobal, 2);
+    } else if (a.sequential) {
+        if (in) AV_GROUP(true, false, kLds, 2);
+        else AV_GROUP(true, false, kGlobal, 2);
+    } else if (ctl) {
+        if (in) AV_GROUP(false, true, kLds, 2);
+        else AV_GROUP(false, true, kGlobal, 2);
+    } else if (wide) {
+        if (in) AV_GROUP(false, false, kLds, 2);
+        else AV_GROUP(false, false, kGlobal, 2);
+    } else {
+        if (in) AV_GROUP(false, false, kLds, 4);
+        else if (where == kEntries) AV_GROUP(false, false, kEntries, 4);
+        else AV_GROUP(false, false, kGlobal, 4);
+    }
+#undef AV_GROUP
 }
 
-// SIMDs of the current device (4 per compute unit), looked up once per device.
+// SIMDs of the current device (4 per compute unit; device_wave_slots counts 8 waves on each).
 int device_simds() {
-    static int simds[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 1024;
-    if (!simds[dev]) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-            return 1024;
-        simds[dev] = 4 * cus;
-    }
-    return simds[dev];
+    const long long slots = device_wave_slots();
+    return slots > 0 ? int(slots / 8) : 1024;
 }
 }  // namespace
 
 hipError_t launch_group_step(const StepArgs &a, hipStream_t s) {
-    const size_t base = group_lds_bytes(a.H, a.C, a.prog.rules_per_set, a.max_pat_h);
-    const size_t prog = sizeof(uint32_t) * (size_t(a.prog.rules_per_set) * kHdrWords +
-                                            a.prog.gmatch_stride + a.prog.rvote_stride +
-                                            2 * (a.C + 1) + a.prog.vote_stride);
-    // the program goes to LDS for launches of 16 steps or more, when it fits and leaves room
-    // for as many waves per CU (160 KiB of LDS) as the batch can use, up to 16 (4 per SIMD)
-    const size_t need = size_t(std::min(16, (a.B + 255) / 256));
-    const size_t budget = std::min(size_t(kLdsBudget), size_t(160) * 1024 / need);
-    const bool prog_lds = a.k >= kShortLaunch && base + prog <= budget;
-    const size_t lds = base + (prog_lds ? prog : 0);
-    const bool narrow = a.max_pat_w <= 3;
-    // at most two waves per SIMD: the 256-VGPR kernels
+    const int Rt = a.prog.rules_per_set, NC = a.sequential ? a.C + 1 : a.C;
+    size_t lds = group_base_bytes(a.H, a.W, a.C, Rt, a.max_pat_h, a.sequential != 0,
+                                  a.ctl.active != 0, a.ctl.random != 0);
+    const size_t rest = sizeof(uint32_t) * size_t(a.prog.gtab_stride - group_head_words(Rt, NC));
+    const size_t entries = sizeof(uint32_t) * size_t(a.prog.gentry_words);
+    // Waves per SIMD the kernel's registers leave room for: two (256 registers) for batches that
+    // need no more, and for sequential order and control, whose steps are long enough that
+    // registers count for more; else four.
     const bool wide = a.B <= 2 * device_simds();
+    const bool two = wide || a.sequential || a.ctl.active;
+    // the lists go to LDS for launches of 16 steps or more, as far as they fit and leave room for
+    // as many waves per CU (160 KiB of LDS) as the batch can use
+    const size_t need = size_t(std::min(two ? 8 : 16, (a.B + 255) / 256));
+    const size_t budget = std::min(size_t(kLdsBudget), kCuLds / need);
+    int where = kGlobal;
+    if (a.k >= kShortLaunch && lds + rest <= budget) {
+        where = kLds;
+        lds += rest;
+    } else if (a.k >= kShortLaunch && !two && lds + entries <= budget) {
+        where = kEntries;
+        lds += entries;
+    }
+    const bool narrow = a.max_pat_w <= 3;
     if (group_rows(a.H) == 16) {
-        if (narrow) launch_rpl<1, 3>(a, lds, prog_lds, wide, s);
-        else launch_rpl<1, 8>(a, lds, prog_lds, wide, s);
+        if (narrow) launch_mode<1, 3>(a, lds, where, wide, s);
+        else launch_mode<1, 8>(a, lds, where, wide, s);
     } else {
-        if (narrow) launch_rpl<2, 3>(a, lds, prog_lds, wide, s);
-        else launch_rpl<2, 8>(a, lds, prog_lds, wide, s);
+        if (narrow) launch_mode<2, 3>(a, lds, where, wide, s);
+        else launch_mode<2, 8>(a, lds, where, wide, s);
     }
     return hipGetLastError();
 }

@@ -500,9 +500,10 @@ size_t wave_lds_bytes(int H, int W, int C, int rules_per_set, bool control, bool
 }
 
 hipError_t launch_wave_step(const StepArgs &a, hipStream_t s) {
-    if (a.prog.gtab && solo_eligible(a.H, a.W, a.C, a.prog.rules_per_set, a.max_pat_h, a.max_pat_w,
-                                     a.sequential != 0, a.ctl.active != 0, a.ctl.random != 0))
-        return launch_solo_step(a, s);
+    if (a.prog.gtab && group_mode_eligible(a.H, a.W, a.C, a.prog.rules_per_set, a.max_pat_h,
+                                           a.max_pat_w, a.sequential != 0, a.ctl.active != 0,
+                                           a.ctl.random != 0))
+        return launch_group_step(a, s);
     WaveLayout L;
     L.Hq = rows_per_group(a.H);
     const int max_threads = a.W <= 32 ? 1024 : 512;
