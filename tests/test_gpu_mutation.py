@@ -128,3 +128,47 @@ def test_evolution_step_end_to_end():
             np.testing.assert_array_equal(d.cpu().numpy(), want_d[t])
     finally:
         b.close()
+
+
+@pytest.mark.parametrize("per", [1920, 2040, 2048, 2050, 4096])
+@pytest.mark.parametrize("shift", [0, 3])
+def test_map_mutation_rows_and_alignment(per, shift):
+    """Individuals around whole workgroups of 256 blocks of eight cells (a grid row each, or
+    packed), at addresses that are no multiple of eight."""
+    require_gpu()
+    import torch
+    C = {1920: 4, 2040: 5, 2048: 4, 2050: 5, 4096: 4}[per]
+    H, W = {1920: (20, 24), 2040: (12, 34), 2048: (16, 32), 2050: (10, 41), 4096: (32, 32)}[per]
+    assert C * H * W == per
+    n = 5
+    maps = np.random.default_rng(per).integers(0, 3, (n, C, H, W)).astype(np.uint8)
+    src = torch.zeros(n * per + shift, dtype=torch.uint8, device="cuda")[shift:].view(n, C, H, W)
+    src.copy_(torch.from_numpy(maps))
+    dst = torch.zeros(n * per + 8, dtype=torch.uint8, device="cuda")
+    for kw in (dict(), dict(map_channels=0b0110)):
+        a, o = both(**kw)
+        av.av_mutate_maps(src, dst[shift:shift + n * per].view(n, C, H, W), a)
+        np.testing.assert_array_equal(dst[shift:shift + n * per].cpu().numpy().reshape(maps.shape),
+                                      oracle.mutate_maps(maps, o))
+        assert not dst[:shift].any() and not dst[shift + n * per:].any()
+
+
+@pytest.mark.parametrize("R,C,mh,mw", [(1, 4, 1, 1), (5, 4, 1, 3), (3, 6, 3, 1), (7, 31, 16, 16),
+                                       (2, 4, 5, 5)])
+def test_rule_mutation_pattern_shapes(R, C, mh, mw):
+    """Patterns whose entries are not a multiple of four, down to a single cell, and the largest."""
+    require_gpu()
+    import torch
+    g = np.random.default_rng(R * mh + mw)
+    S = 3
+    shape = np.stack([g.integers(1, mh + 1, (S, R)), g.integers(1, mw + 1, (S, R))], -1)
+    shape = shape.astype(np.int32)
+    ip, op = (g.integers(-1, 2, (S, R, C + 1, mh, mw)).astype(np.int8) for _ in range(2))
+    rw = g.integers(-9, 9, (S, R)).astype(np.int32)
+    dev = [torch.from_numpy(x).cuda() for x in (shape, ip, op, rw)]
+    for kw in (dict(entry_p32=0xC0000000), dict(entry_channels=0b101, entry_p32=0xFFFFFFFF)):
+        a, o = both(**kw)
+        out = [torch.empty_like(x) for x in dev[1:]]
+        av.av_mutate_rules(*dev, *out, a)
+        for g_, w_ in zip(out, oracle.mutate_rules(shape, ip, op, rw, o)):
+            np.testing.assert_array_equal(g_.cpu().numpy(), w_)
