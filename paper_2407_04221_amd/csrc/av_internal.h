@@ -198,33 +198,57 @@ struct SearchArgs {
     uint64_t mask = 0;                             // slots - 1
     uint64_t hash_mask = ~0ull;                    // bits of the map hash that are used
     uint64_t *best = nullptr;                      // packed (reward, -visit)
-    uint32_t *counts = nullptr;                    // terminal, overflow, survivors
+    uint32_t *counts = nullptr;                    // terminal, overflow, survivors, new nodes
     int32_t *block_count = nullptr;                // [ceil(n / 256)]
     int32_t *src_of = nullptr;                     // [cap] child of each next-frontier node
     int32_t *next_reward = nullptr, *next_depth = nullptr;           // [cap]
     void *next = nullptr;                          // next frontier rows [C][next_n][H]
     int32_t next_n = 0, next_off = 0;              // its block count and first block written
-    int64_t *root_slot = nullptr;                  // root_kernel: the root's table slot
 };
-// phase 0 gather, 1 post/claim/flag/scan/place, 2 copy rows (nn nodes), 3 root insert.
+// Best-first: the node pool, the open list and the next new nodes (pool null: level order).
+struct BestFirstArgs {
+    void *pool = nullptr;                          // [C][pcap][H] rows
+    int32_t pcap = 0, pool_n = 0;
+    int32_t *pool_reward = nullptr, *pool_depth = nullptr;
+    uint64_t *pool_val = nullptr;
+    int64_t *pool_slot = nullptr;
+    uint64_t *open_keys = nullptr;
+    uint32_t *open_ids = nullptr;
+    int32_t *parents = nullptr;                    // the popped nodes
+    uint64_t *new_keys = nullptr;                  // [n] the level's survivors, sorted
+    uint32_t *new_ids = nullptr;
+};
+// What the host learns from a level (pinned host memory the kernels write).
+struct SearchResult {
+    uint64_t best;
+    uint32_t terminal, overflow, survivors;        // in the order of SearchArgs::counts
+    uint32_t parents;                              // best-first: the next iteration's
+};
+hipError_t launch_root(const SearchArgs &a, const BestFirstArgs &f, int row_bytes,
+                       const void *front, hipStream_t s);
+// A level whose post .. copy phases run in one workgroup.
+bool small_level(const SearchArgs &a, int row_bytes);
+hipError_t launch_small_level(const SearchArgs &a, const BestFirstArgs &f, int row_bytes,
+                              const void *kids, SearchResult *host, hipStream_t s);
+// phase 0 gather, 1 post/claim/flag/scan/place, 2 copy rows (nn nodes).
 hipError_t launch_search_phase(const SearchArgs &a, int row_bytes, const void *front, int nf,
                                void *kids, int32_t *kid_t, hipStream_t s, int phase, int nn);
 
 // Batched best-first pieces (k_search.hip).
 hipError_t launch_copy_rows(int row_bytes, const void *src, int nsrc, const int32_t *src_of,
                             void *dst, int ndst, int off, int n, int C, int H, hipStream_t s);
-hipError_t launch_bf_pop(const uint32_t *open_ids, int kp, const int64_t *pool_slot,
-                         const uint64_t *pool_val, const uint64_t *vals, int32_t *parents,
-                         uint32_t *n_par, uint32_t *counts, hipStream_t s);
-hipError_t launch_bf_gather_meta(const int32_t *parents, int np, const int32_t *pool_reward,
-                                 const int32_t *pool_depth, int32_t *front_reward,
-                                 int32_t *front_depth, hipStream_t s);
+hipError_t launch_bf_pop(const uint32_t *open_ids, int K, int m, const uint32_t *new_n,
+                         const int64_t *pool_slot, const uint64_t *pool_val, const uint64_t *vals,
+                         int32_t *parents, SearchResult *host, uint32_t *counts, hipStream_t s);
+hipError_t launch_bf_gather(int row_bytes, const BestFirstArgs &f, int np, void *front,
+                            int32_t *front_reward, int32_t *front_depth, int C, int H,
+                            hipStream_t s);
 hipError_t launch_bf_append(const int32_t *src_of, int nn, int pool_n, const uint64_t *kid_val,
                             const int64_t *slot, uint64_t *pool_val, int64_t *pool_slot,
                             uint64_t *new_keys, uint32_t *new_ids, hipStream_t s);
 hipError_t launch_bf_merge(const uint64_t *ok, const uint32_t *oi, int m, const uint64_t *nk,
-                           const uint32_t *ni, int nn, uint64_t *outk, uint32_t *outi,
-                           hipStream_t s);
+                           const uint32_t *ni, int nn, const uint32_t *new_n, uint64_t *outk,
+                           uint32_t *outi, hipStream_t s);
 hipError_t launch_bf_open(int row_bytes, const void *pool, int pcap, const uint32_t *ids, int n,
                           int C, int H, int W, uint8_t *maps, const int32_t *pool_reward,
                           const int32_t *pool_depth, int32_t *reward, int32_t *depth,

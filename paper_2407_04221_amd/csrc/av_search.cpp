@@ -1,7 +1,8 @@
 // Batched search (include/autoverse.h, av_search_*): host side.  Owns a children batch
 // (stepped with the batch engines), two frontier buffers, the hash table and the per-level
 // scratch arrays; each level runs gather -> step -> post/claim/flag/scan/place -> copy on the
-// search's stream with one synchronisation to learn the next frontier's size.
+// search's stream with one synchronisation to learn the next frontier's size (small levels: one
+// kernel behind the step).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -44,8 +45,10 @@ struct av_search_s {
     uint64_t *pool_val = nullptr, *new_keys = nullptr;
     int64_t *pool_slot = nullptr;
     uint64_t *okeys[2] = {nullptr, nullptr};
-    uint32_t *oids[2] = {nullptr, nullptr}, *new_ids = nullptr, *n_par = nullptr;
+    uint32_t *oids[2] = {nullptr, nullptr}, *new_ids = nullptr;
     int ocur = 0;
+    int64_t npar = 0;                // popped for the next iteration (in parents)
+    SearchResult *res = nullptr, *d_res = nullptr;   // pinned host memory, and for the kernels
 };
 
 namespace {
@@ -60,6 +63,8 @@ namespace {
         }                                                                                \
     } while (0)
 
+constexpr size_t kSlotBytes = 3 * sizeof(uint64_t) + sizeof(uint32_t);   // keys, vals, claim, epoch
+
 template <typename T>
 hipError_t alloc(T **p, size_t count) {
     return hipMalloc(reinterpret_cast<void **>(p), std::max<size_t>(count, 1) * sizeof(T));
@@ -68,13 +73,13 @@ hipError_t alloc(T **p, size_t count) {
 void release(av_search_t s) {
     void *ptrs[] = {s->front[0], s->front[1], s->reward[0], s->reward[1], s->depth[0], s->depth[1],
                     s->actions, s->rew, s->done, s->kid_reward, s->kid_depth, s->block_count,
-                    s->src_of, s->kid_val, s->slot, s->keys, s->vals, s->claim, s->best, s->epoch,
-                    s->counts, s->store, s->pool, s->pool_reward, s->pool_depth, s->parents,
+                    s->src_of, s->kid_val, s->slot, s->keys, s->best, s->counts, s->store, s->pool, s->pool_reward, s->pool_depth, s->parents,
                     s->pool_val,
                     s->new_keys, s->pool_slot, s->okeys[0], s->okeys[1], s->oids[0], s->oids[1],
-                    s->new_ids, s->n_par};
+                    s->new_ids};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
+    if (s->res) (void)hipHostFree(s->res);
     if (s->kids) av_destroy_batch(s->kids);
 }
 
@@ -98,6 +103,18 @@ SearchArgs level_args(av_search_t s, int n) {
     return a;
 }
 
+BestFirstArgs best_first_args(av_search_t s) {
+    BestFirstArgs f;
+    if (s->K == 0) return f;
+    f.pool = s->pool; f.pcap = int32_t(s->pcap); f.pool_n = int32_t(s->pool_n);
+    f.pool_reward = s->pool_reward; f.pool_depth = s->pool_depth;
+    f.pool_val = s->pool_val; f.pool_slot = s->pool_slot;
+    f.open_keys = s->okeys[s->ocur]; f.open_ids = s->oids[s->ocur];
+    f.parents = s->parents;
+    f.new_keys = s->new_keys; f.new_ids = s->new_ids;
+    return f;
+}
+
 // best node word: (reward with its sign bit flipped) << 32 | ~visit
 av_status decode_best(uint64_t best, av_search_info *info) {
     info->best_reward = int32_t(uint32_t(best >> 32) ^ 0x80000000u);
@@ -106,10 +123,20 @@ av_status decode_best(uint64_t best, av_search_info *info) {
 }
 
 av_status read_best(av_search_t s, av_search_info *info) {
-    uint64_t best = 0;
-    SEARCH_HIP(hipMemcpyAsync(&best, s->best, sizeof best, hipMemcpyDeviceToHost, s->stream));
+    SEARCH_HIP(hipMemcpyAsync(&s->res->best, s->best, sizeof s->res->best, hipMemcpyDeviceToHost,
+                              s->stream));
     SEARCH_HIP(hipStreamSynchronize(s->stream));
-    return decode_best(best, info);
+    return decode_best(s->res->best, info);
+}
+
+// The counts and the best node of a level run by launch_search_phase, into s->res.
+av_status read_level(av_search_t s) {
+    SEARCH_HIP(hipMemcpyAsync(&s->res->terminal, s->counts, 3 * sizeof(uint32_t),
+                              hipMemcpyDeviceToHost, s->stream));
+    SEARCH_HIP(hipMemcpyAsync(&s->res->best, s->best, sizeof s->res->best, hipMemcpyDeviceToHost,
+                              s->stream));
+    SEARCH_HIP(hipStreamSynchronize(s->stream));
+    return AV_OK;
 }
 
 }  // namespace
@@ -172,14 +199,19 @@ av_status av_search_create(const av_search_config *cfg, av_search_t *out) {
     if (e == hipSuccess) e = alloc(&s->slot, nk);
     if (e == hipSuccess) e = alloc(&s->block_count, (nk + 255) / 256);
     if (e == hipSuccess) e = alloc(&s->src_of, nk);      // survivors of one level: <= children
-    if (e == hipSuccess) e = alloc(&s->keys, s->slots);
-    if (e == hipSuccess) e = alloc(&s->vals, s->slots);
-    if (e == hipSuccess) e = alloc(&s->claim, s->slots);
-    if (e == hipSuccess) e = alloc(&s->epoch, s->slots);
+    // keys, vals, claim and epoch side by side: cleared by one fill
+    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&s->keys), s->slots * kSlotBytes);
+    s->vals = s->keys + s->slots;
+    s->claim = s->vals + s->slots;
+    s->epoch = reinterpret_cast<uint32_t *>(s->claim + s->slots);
     if (e == hipSuccess)
         e = hipMalloc(&s->store, s->slots * size_t(c.channels) * c.height * s->row_bytes);
     if (e == hipSuccess) e = alloc(&s->best, 1);
-    if (e == hipSuccess) e = alloc(&s->counts, 3);
+    if (e == hipSuccess) e = alloc(&s->counts, 4);
+    if (e == hipSuccess)
+        e = hipHostMalloc(reinterpret_cast<void **>(&s->res), sizeof *s->res, hipHostMallocMapped);
+    if (e == hipSuccess)
+        e = hipHostGetDevicePointer(reinterpret_cast<void **>(&s->d_res), s->res, 0);
     if (e == hipSuccess && s->K > 0) {
         s->pcap = c.max_nodes;
         const size_t pbytes = size_t(c.channels) * s->pcap * c.height * s->row_bytes;
@@ -195,7 +227,6 @@ av_status av_search_create(const av_search_config *cfg, av_search_t *out) {
         if (e == hipSuccess) e = alloc(&s->new_keys, nk);
         if (e == hipSuccess) e = alloc(&s->new_ids, nk);
         if (e == hipSuccess) e = alloc(&s->parents, 512);
-        if (e == hipSuccess) e = alloc(&s->n_par, 1);
     }
     if (e == hipSuccess) {
         std::vector<uint8_t> acts(nk);
@@ -231,31 +262,17 @@ av_status av_search_begin(av_search_t s, const uint8_t *root) {
     s->cur = 0;
     SEARCH_HIP(launch_pack(root, s->front[0], nullptr, 1, c.channels, c.height, c.width,
                            s->row_bytes, s->stream));
-    SEARCH_HIP(hipMemsetAsync(s->reward[0], 0, sizeof(int32_t), s->stream));
-    SEARCH_HIP(hipMemsetAsync(s->depth[0], 0, sizeof(int32_t), s->stream));
-    SEARCH_HIP(hipMemsetAsync(s->keys, 0, s->slots * sizeof(uint64_t), s->stream));
-    SEARCH_HIP(hipMemsetAsync(s->vals, 0, s->slots * sizeof(uint64_t), s->stream));
-    SEARCH_HIP(hipMemsetAsync(s->claim, 0, s->slots * sizeof(uint64_t), s->stream));
-    SEARCH_HIP(hipMemsetAsync(s->epoch, 0, s->slots * sizeof(uint32_t), s->stream));
-    SEARCH_HIP(hipMemsetAsync(s->counts, 0, 3 * sizeof(uint32_t), s->stream));
+    SEARCH_HIP(hipMemsetAsync(s->keys, 0, s->slots * kSlotBytes, s->stream));
+    s->ocur = 0;
+    s->pool_n = 0;
     SearchArgs a = level_args(s, 1);
-    if (s->K > 0) a.root_slot = s->pool_slot;            // the root is pool node 0
-    SEARCH_HIP(launch_search_phase(a, s->row_bytes, s->front[0], 1, nullptr, nullptr, s->stream, 3,
-                                   0));
+    a.next_reward = s->reward[0];
+    a.next_depth = s->depth[0];
+    SEARCH_HIP(launch_root(a, best_first_args(s), s->row_bytes, s->front[0], s->stream));
     if (s->K > 0) {
-        const uint64_t v0 = (uint64_t(0x80000000u) << 32) | 0xFFFFFFFFull;   // (reward 0, depth 0)
-        SEARCH_HIP(hipMemsetAsync(s->parents, 0, sizeof(int32_t), s->stream));
-        SEARCH_HIP(launch_copy_rows(s->row_bytes, s->front[0], 1, s->parents, s->pool, int(s->pcap),
-                                    0, 1, c.channels, c.height, s->stream));
-        SEARCH_HIP(hipMemsetAsync(s->pool_reward, 0, sizeof(int32_t), s->stream));
-        SEARCH_HIP(hipMemsetAsync(s->pool_depth, 0, sizeof(int32_t), s->stream));
-        SEARCH_HIP(hipMemcpyAsync(s->pool_val, &v0, sizeof v0, hipMemcpyHostToDevice, s->stream));
-        SEARCH_HIP(hipMemcpyAsync(s->okeys[0], &v0, sizeof v0, hipMemcpyHostToDevice, s->stream));
-        SEARCH_HIP(hipMemsetAsync(s->oids[0], 0, sizeof(uint32_t), s->stream));
-        SEARCH_HIP(hipStreamSynchronize(s->stream));      // v0 lives on this stack frame
-        s->ocur = 0;
         s->pool_n = 1;
         s->open_n = 1;
+        s->npar = 1;                                      // the root
     }
     s->n_front = 1;
     s->level = 0;
@@ -277,27 +294,25 @@ av_status expand_best_first(av_search_t s, int64_t max_children, av_search_info 
         info->visited = s->visited;
         return read_best(s, info);
     }
-    uint32_t npar = 0;
-    SEARCH_HIP(launch_bf_pop(s->oids[s->ocur], kp, s->pool_slot, s->pool_val, s->vals, s->parents,
-                             s->n_par, s->counts, s->stream));
-    SEARCH_HIP(hipMemcpyAsync(&npar, s->n_par, sizeof npar, hipMemcpyDeviceToHost, s->stream));
-    SEARCH_HIP(hipStreamSynchronize(s->stream));
+    // the parents were popped when the last iteration ended: the first kp of the open list
+    const int64_t npar = s->npar;
     const int64_t n = std::min<int64_t>(int64_t(s->A) * npar, max_children);
     if (s->visited + n > int64_t(0xFFFFFFFEll))
         return set_error(AV_EINVAL, "a search may visit at most 2^32 - 2 states");
+    const int64_t m = s->open_n - kp;
     int64_t nn = 0;
-    uint32_t counts[3] = {0, 0, 0};
-    uint64_t best = 0;                 // read with the counts: final once the children are posted
+    uint32_t terminal = 0;
+    bool small = false;
     if (n > 0) {
         s->cur = 0;
-        SEARCH_HIP(launch_copy_rows(s->row_bytes, s->pool, int(s->pcap), s->parents, s->front[0],
-                                    int(npar), 0, int(npar), c.channels, c.height, s->stream));
-        SEARCH_HIP(launch_bf_gather_meta(s->parents, int(npar), s->pool_reward, s->pool_depth,
-                                         s->reward[0], s->depth[0], s->stream));
+        const BestFirstArgs f = best_first_args(s);
+        SEARCH_HIP(launch_bf_gather(s->row_bytes, f, int(npar), s->front[0], s->reward[0],
+                                    s->depth[0], c.channels, c.height, s->stream));
         SearchArgs a = level_args(s, int(n));
         a.cap = int(s->pcap - s->pool_n);
         a.next_reward = s->pool_reward + s->pool_n;
         a.next_depth = s->pool_depth + s->pool_n;
+        a.next = s->pool;
         void *kst = batch_state(s->kids);           // (bf_pop cleared the counts)
         if (batch_engine(s->kids) == AV_ENGINE_LANE16) {
             if (av_status st = step_prefix(s->kids, int(n), s->actions, s->rew, s->done,
@@ -308,45 +323,67 @@ av_status expand_best_first(av_search_t s, int64_t max_children, av_search_info 
                                            batch_counters(s->kids), s->stream, 0, 0));
             if (av_status st = step_prefix(s->kids, int(n), s->actions, s->rew, s->done)) return st;
         }
-        SEARCH_HIP(launch_search_phase(a, s->row_bytes, s->front[0], int(npar), kst, nullptr,
-                                       s->stream, 1, 0));
-        SEARCH_HIP(hipMemcpyAsync(counts, s->counts, sizeof counts, hipMemcpyDeviceToHost,
-                                  s->stream));
-        SEARCH_HIP(hipMemcpyAsync(&best, s->best, sizeof best, hipMemcpyDeviceToHost, s->stream));
-        SEARCH_HIP(hipStreamSynchronize(s->stream));
-        if (counts[1] || int64_t(counts[2]) > s->pcap - s->pool_n) {
+        small = small_level(a, s->row_bytes);
+        if (small) {
+            // the new nodes are counted on the device: merge and pop read the count there
+            const uint32_t *new_n = s->counts + 3;
+            SEARCH_HIP(launch_small_level(a, f, s->row_bytes, kst, s->d_res, s->stream));
+            SEARCH_HIP(launch_bf_merge(s->okeys[s->ocur] + kp, s->oids[s->ocur] + kp, int(m),
+                                       s->new_keys, s->new_ids, int(n), new_n,
+                                       s->okeys[1 - s->ocur], s->oids[1 - s->ocur], s->stream));
+            SEARCH_HIP(launch_bf_pop(s->oids[1 - s->ocur], s->K, int(m), new_n, s->pool_slot,
+                                     s->pool_val, s->vals, s->parents, s->d_res, s->counts,
+                                     s->stream));
+            SEARCH_HIP(hipStreamSynchronize(s->stream));
+        } else {
+            SEARCH_HIP(launch_search_phase(a, s->row_bytes, s->front[0], int(npar), kst, nullptr,
+                                           s->stream, 1, 0));
+            if (av_status st = read_level(s)) return st;
+        }
+        const uint32_t overflow = s->res->overflow;
+        nn = s->res->survivors;
+        terminal = s->res->terminal;
+        if (overflow || nn > s->pcap - s->pool_n) {
             s->begun = false;
-            return set_error(AV_ENOMEM, counts[1]
+            return set_error(AV_ENOMEM, overflow
                                             ? "search table too full (an insertion probed 4096 "
                                               "slots); use a larger table_log2 and call "
                                               "av_search_begin again"
                                             : "best-first node pool full; use a larger max_nodes "
                                               "and call av_search_begin again");
         }
-        nn = counts[2];
-        SEARCH_HIP(launch_copy_rows(s->row_bytes, kst, int(n), s->src_of, s->pool, int(s->pcap),
-                                    int(s->pool_n), int(nn), c.channels, c.height, s->stream));
-        SEARCH_HIP(launch_bf_append(s->src_of, int(nn), int(s->pool_n), s->kid_val, s->slot,
-                                    s->pool_val, s->pool_slot, s->new_keys, s->new_ids,
-                                    s->stream));
+        if (!small) {
+            SEARCH_HIP(launch_copy_rows(s->row_bytes, kst, int(n), s->src_of, s->pool,
+                                        int(s->pcap), int(s->pool_n), int(nn), c.channels,
+                                        c.height, s->stream));
+            SEARCH_HIP(launch_bf_append(s->src_of, int(nn), int(s->pool_n), s->kid_val, s->slot,
+                                        s->pool_val, s->pool_slot, s->new_keys, s->new_ids,
+                                        s->stream));
+        }
         s->pool_n += nn;
     }
-    const int64_t m = s->open_n - kp;
-    SEARCH_HIP(launch_bf_merge(s->okeys[s->ocur] + kp, s->oids[s->ocur] + kp, int(m), s->new_keys,
-                               s->new_ids, int(nn), s->okeys[1 - s->ocur], s->oids[1 - s->ocur],
-                               s->stream));
-    s->ocur = 1 - s->ocur;
     s->open_n = m + nn;
+    if (n == 0 || !small) {
+        SEARCH_HIP(launch_bf_merge(s->okeys[s->ocur] + kp, s->oids[s->ocur] + kp, int(m),
+                                   s->new_keys, s->new_ids, int(nn), nullptr,
+                                   s->okeys[1 - s->ocur], s->oids[1 - s->ocur], s->stream));
+        SEARCH_HIP(launch_bf_pop(s->oids[1 - s->ocur], s->K, int(s->open_n), nullptr, s->pool_slot,
+                                 s->pool_val, s->vals, s->parents, s->d_res, s->counts,
+                                 s->stream));
+        SEARCH_HIP(hipStreamSynchronize(s->stream));
+    }
+    s->npar = s->res->parents;
+    s->ocur = 1 - s->ocur;
     s->visited += n;
     s->level += 1;
     info->parents = npar;
     info->children = n;
-    info->terminal = counts[0];
+    info->terminal = terminal;
     info->survivors = nn;
     info->level = s->level;
     info->frontier = s->open_n;
     info->visited = s->visited;
-    return n > 0 ? decode_best(best, info) : read_best(s, info);
+    return n > 0 ? decode_best(s->res->best, info) : read_best(s, info);
 }
 
 }  // namespace
@@ -361,14 +398,13 @@ av_status av_search_expand(av_search_t s, int64_t max_children, av_search_info *
     if (s->K > 0) return expand_best_first(s, max_children, info);
     info->parents = s->n_front;
     const int64_t n = std::min<int64_t>(int64_t(s->A) * s->n_front, max_children);
-    uint64_t best = 0;                 // read with the counts: final once the children are posted
     if (s->visited + n > int64_t(0xFFFFFFFEll))
         return set_error(AV_EINVAL, "a search may visit at most 2^32 - 2 states");
     if (n > 0) {
-        const av_search_config &c = s->cfg;
         SearchArgs a = level_args(s, int(n));
         void *kst = batch_state(s->kids);
-        SEARCH_HIP(hipMemsetAsync(s->counts, 0, 3 * sizeof(uint32_t), s->stream));
+        const bool small = small_level(a, s->row_bytes);
+        if (!small) SEARCH_HIP(hipMemsetAsync(s->counts, 0, 3 * sizeof(uint32_t), s->stream));
         if (batch_engine(s->kids) == AV_ENGINE_LANE16) {
             // the lane16 step reads each child's parent rows and depth itself
             if (av_status st = step_prefix(s->kids, int(n), s->actions, s->rew, s->done,
@@ -380,36 +416,38 @@ av_status av_search_expand(av_search_t s, int64_t max_children, av_search_info *
                                            batch_counters(s->kids), s->stream, 0, 0));
             if (av_status st = step_prefix(s->kids, int(n), s->actions, s->rew, s->done)) return st;
         }
-        SEARCH_HIP(launch_search_phase(a, s->row_bytes, s->front[s->cur], int(s->n_front), kst,
-                                       nullptr, s->stream, 1, 0));
-        uint32_t counts[3];
-        SEARCH_HIP(hipMemcpyAsync(counts, s->counts, sizeof counts, hipMemcpyDeviceToHost,
-                                  s->stream));
-        SEARCH_HIP(hipMemcpyAsync(&best, s->best, sizeof best, hipMemcpyDeviceToHost, s->stream));
-        SEARCH_HIP(hipStreamSynchronize(s->stream));
-        if (counts[1]) {
+        if (small) {
+            SEARCH_HIP(launch_small_level(a, best_first_args(s), s->row_bytes, kst, s->d_res,
+                                          s->stream));
+            SEARCH_HIP(hipStreamSynchronize(s->stream));
+        } else {
+            SEARCH_HIP(launch_search_phase(a, s->row_bytes, s->front[s->cur], int(s->n_front), kst,
+                                           nullptr, s->stream, 1, 0));
+            if (av_status st = read_level(s)) return st;
+        }
+        if (s->res->overflow) {
             s->begun = false;
             return set_error(AV_ENOMEM, "search table too full (an insertion probed 4096 slots); "
                                         "use a larger table_log2 and call av_search_begin again");
         }
-        const int64_t nn = std::min<int64_t>(counts[2], s->cap);
+        const int64_t nn = std::min<int64_t>(s->res->survivors, s->cap);
         a.next_n = int(nn);
         a.next_off = 0;
-        SEARCH_HIP(launch_search_phase(a, s->row_bytes, s->front[s->cur], int(s->n_front), kst,
-                                       nullptr, s->stream, 2, int(nn)));
+        if (!small)
+            SEARCH_HIP(launch_search_phase(a, s->row_bytes, s->front[s->cur], int(s->n_front), kst,
+                                           nullptr, s->stream, 2, int(nn)));
         s->cur = 1 - s->cur;
         s->n_front = nn;
         s->visited += n;
         s->level += 1;
         info->children = n;
-        info->terminal = counts[0];
-        info->survivors = counts[2];
-        (void)c;
+        info->terminal = s->res->terminal;
+        info->survivors = s->res->survivors;
     }
     info->level = s->level;
     info->frontier = s->n_front;
     info->visited = s->visited;
-    return n > 0 ? decode_best(best, info) : read_best(s, info);
+    return n > 0 ? decode_best(s->res->best, info) : read_best(s, info);
 }
 
 av_status av_search_frontier(av_search_t s, uint8_t *maps, int32_t *reward, int32_t *depth) {

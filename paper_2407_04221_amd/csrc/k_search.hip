@@ -38,6 +38,11 @@ namespace {
 constexpr uint32_t kMaxProbe = 4096;   // longest probe sequence before the table counts as full
 constexpr uint32_t kPending = 0x80000000u;     // owner word: taken this level by child (low bits)
 constexpr uint32_t kPublished = 0x40000000u;   // owner word: the map is in the slot's store entry
+// A level is one workgroup's (small_level_kernel) up to these children and bytes of their maps:
+// one compute unit reads the maps about three times, which up to here costs less than the
+// launches it saves.
+constexpr int kSmallLevel = 1024;
+constexpr size_t kSmallLevelBytes = 512 * 1024;
 
 template <typename RowT>
 __device__ inline uint64_t row_at(const void *base, size_t idx) {
@@ -219,6 +224,25 @@ __global__ void __launch_bounds__(256) post_kernel(SearchArgs a, const void *kid
     a.kid_val[i] = v;
 }
 
+// Child i's map into the store entry of slot s.
+template <typename RowT>
+__device__ inline void store_map(const SearchArgs &a, const void *kids, int i, int64_t s) {
+    RowT *dst = reinterpret_cast<RowT *>(static_cast<char *>(a.store) +
+                                         size_t(s) * a.C * a.H * sizeof(RowT));
+    const RowT *src = static_cast<const RowT *>(kids);
+    if ((a.H * sizeof(RowT)) % 16 == 0) {              // 16 bytes at a time (see same_map)
+        const int q = int(a.H * sizeof(RowT) / 16);
+        for (int c = 0; c < a.C; ++c) {
+            const uint4 *from = reinterpret_cast<const uint4 *>(src + (size_t(c) * a.n + i) * a.H);
+            uint4 *to = reinterpret_cast<uint4 *>(dst + size_t(c) * a.H);
+            for (int k = 0; k < q; ++k) to[k] = from[k];
+        }
+    } else {
+        for (int c = 0; c < a.C; ++c)
+            for (int y = 0; y < a.H; ++y) dst[c * a.H + y] = src[(size_t(c) * a.n + i) * a.H + y];
+    }
+}
+
 template <typename RowT>
 __global__ void __launch_bounds__(256) claim_kernel(SearchArgs a, const void *kids) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -230,20 +254,7 @@ __global__ void __launch_bounds__(256) claim_kernel(SearchArgs a, const void *ki
     // only to see that it is not theirs; the next level sees both)
     const uint64_t key = a.keys[s];
     if (uint32_t(key) == (kPending | uint32_t(i))) {
-        RowT *dst = reinterpret_cast<RowT *>(static_cast<char *>(a.store) +
-                                             size_t(s) * a.C * a.H * sizeof(RowT));
-        const RowT *src = static_cast<const RowT *>(kids);
-        if ((a.H * sizeof(RowT)) % 16 == 0) {          // 16 bytes at a time (see same_map)
-            const int q = int(a.H * sizeof(RowT) / 16);
-            for (int c = 0; c < a.C; ++c) {
-                const uint4 *from = reinterpret_cast<const uint4 *>(src + (size_t(c) * a.n + i) * a.H);
-                uint4 *to = reinterpret_cast<uint4 *>(dst + size_t(c) * a.H);
-                for (int k = 0; k < q; ++k) to[k] = from[k];
-            }
-        } else {
-            for (int c = 0; c < a.C; ++c)
-                for (int y = 0; y < a.H; ++y) dst[c * a.H + y] = src[(size_t(c) * a.n + i) * a.H + y];
-        }
+        store_map<RowT>(a, kids, i, s);
         a.keys[s] = (key & 0xFFFFFFFF00000000ull) | kPublished;
     }
     if (a.vals[s] == a.kid_val[i] && a.epoch[s] == a.cur_epoch)
@@ -325,44 +336,6 @@ __global__ void __launch_bounds__(256) place_kernel(SearchArgs a, int cap) {
     a.next_depth[pos] = a.kid_depth[i];
 }
 
-// Rows of blocks src_of[q] of a [C][n][H] buffer into blocks off + q of a [C][ndst][H] one.
-template <typename RowT>
-__global__ void __launch_bounds__(256) copy_kernel(const void *kids, int n, void *next, int nn,
-                                                   const int32_t *src_of, int C, int H, int ndst,
-                                                   int off) {
-    const size_t r = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (r >= size_t(C) * nn * H) return;
-    const int y = int(r % H);
-    const size_t cq = r / H;
-    const int q = int(cq % nn), c = int(cq / nn);
-    static_cast<RowT *>(next)[(size_t(c) * ndst + off + q) * H + y] =
-        static_cast<const RowT *>(kids)[(size_t(c) * n + src_of[q]) * H + y];
-}
-
-template <typename RowT>
-__global__ void root_kernel(SearchArgs a, const void *front) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    // the table is empty: the root takes its home slot, published at once
-    const uint64_t h = map_hash<RowT>(front, 0, 1, a.C, a.H) & a.hash_mask;
-    const uint64_t s = h & a.mask;
-    RowT *dst = reinterpret_cast<RowT *>(static_cast<char *>(a.store) +
-                                         size_t(s) * a.C * a.H * sizeof(RowT));
-    for (int r = 0; r < a.C * a.H; ++r) dst[r] = static_cast<const RowT *>(front)[r];
-    a.keys[s] = (uint64_t(hash_tag(h)) << 32) | kPublished;
-    a.vals[s] = pack_value(0, 0);
-    *a.best = (uint64_t(0x80000000u) << 32) | 0xFFFFFFFFull;
-    if (a.root_slot) *a.root_slot = s;
-}
-
-// ---------------------------------------------------------------------------------------
-// Batched best-first (av_search_config.best_first_k > 0).  Nodes live in a pool ([C][P][H]
-// rows plus reward, depth, packed (reward, -depth) value and table slot per node id); the
-// open list holds (value, id) pairs sorted by value descending, ties by id ascending.  An
-// iteration pops its first k entries, keeps those whose value is still their slot's value
-// (the others were beaten by a later copy of their state), expands them in id order with the
-// level kernels above, appends the survivors to the pool with the next ids, sorts them, and
-// merges them into the rest of the open list.
-
 // In-block exclusive prefix of 0/1 flags for any multiple of 64 threads (up to 1024).
 __device__ inline int block_prefix_any(int flag, int *sums, int &prefix) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
@@ -379,15 +352,214 @@ __device__ inline int block_prefix_any(int flag, int *sums, int &prefix) {
     return total;
 }
 
-// Pop: the first kp open ids, sorted ascending (bitonic, 512 slots), those still alive
-// compacted into parents[]; *n_par = their number.  One workgroup of 512 threads.
-__global__ void __launch_bounds__(512) bf_pop_kernel(const uint32_t *open_ids, int kp,
+template <typename T>
+__device__ inline T load_shared(const T *p) {          // past the first-level cache
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline void store_shared(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Blocks from[q] of a [C][n][per] buffer into blocks off + q of a [C][ndst][per] one, by the
+// whole workgroup.
+template <typename V>
+__device__ inline void copy_blocks(const V *src, int n, V *dst, int ndst, int off, int kept,
+                                   int per, int C, const int32_t *from) {
+    const uint32_t row = uint32_t(kept) * uint32_t(per), all = row * uint32_t(C);
+    for (uint32_t r = threadIdx.x; r < all; r += blockDim.x) {
+        const uint32_t c = r / row, in = r - c * row, q = in / uint32_t(per);
+        const uint32_t y = in - q * uint32_t(per);
+        dst[(size_t(c) * ndst + off + q) * per + y] = src[(size_t(c) * n + from[q]) * per + y];
+    }
+}
+
+// A whole level of at most kSmallLevel children in one workgroup, one child per thread: post,
+// claim, flag, scan, place and copy of the survivors, with barriers where the kernels above end,
+// and with f.pool also the new nodes' pool entries and their sorted (value, id) list.  A level
+// this small is bound by the time between kernels, not by the work: the six kernels, a fill, two
+// copies to the host and a second synchronisation of a best-first iteration, which took nearly
+// all of its time, are one launch and one wait.  Measured (MI355X): best-first, 32 parents, 8000
+// visits of 13 x 11 maps 7716 -> 3904 us; level order, 200000 visits of 16 x 16 maps, four of
+// eight levels this small, 935 -> 588 us.  What other threads of the level
+// wrote (the table's value, epoch and claim words) is read past the first-level cache.
+template <typename RowT>
+__global__ void __launch_bounds__(kSmallLevel) small_level_kernel(SearchArgs a, BestFirstArgs f,
+                                                                  const void *kids,
+                                                                  SearchResult *host) {
+    __shared__ uint64_t key[kSmallLevel];
+    __shared__ int32_t src[kSmallLevel];
+    __shared__ int sums[kSmallLevel / 64];
+    __shared__ uint32_t terminal, bad;
+    const int i = threadIdx.x;
+    const bool in = i < a.n;
+    if (i == 0) terminal = bad = 0u;
+    __syncthreads();
+
+    int32_t reward = 0, depth = 0;
+    unsigned long long top = 0;
+    bool over = false;
+    if (in) {
+        const int p = i / a.A;
+        reward = a.front_reward[p] + int32_t(a.rew[i]);
+        depth = a.front_depth[p] + 1;
+        top = (static_cast<unsigned long long>(uint32_t(reward) ^ 0x80000000u) << 32) |
+              (0xFFFFFFFFull - (a.visited + 1 + uint64_t(i)));
+        over = a.done[i] != 0;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long other = __shfl_xor(top, o);
+        top = top > other ? top : other;
+    }
+    const uint64_t ended = __ballot(over);
+    if ((i & 63) == 0) {
+        atomicMax(reinterpret_cast<unsigned long long *>(a.best), top);
+        if (ended) atomicAdd(&terminal, uint32_t(__popcll(ended)));
+    }
+    int64_t s = -1;
+    bool fresh = false;
+    uint64_t v = 0, tag = 0;
+    if (in && !over) {
+        const uint64_t h = map_hash<RowT>(kids, i, a.n, a.C, a.H) & a.hash_mask;
+        tag = uint64_t(hash_tag(h)) << 32;
+        s = probe_exact<RowT>(a, kids, i, h, &fresh);
+        if (s < 0) {
+            atomicOr(&bad, 1u);
+        } else {
+            v = pack_value(reward, depth);
+            const uint64_t old = atomicMax(reinterpret_cast<unsigned long long *>(&a.vals[s]),
+                                           static_cast<unsigned long long>(v));
+            if (old < v) store_shared(&a.epoch[s], a.cur_epoch);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    // claim; publish a slot this child took (all probes are done)
+    const unsigned long long stamp =
+        (static_cast<unsigned long long>(a.cur_epoch) << 32) | (0xFFFFFFFFu - uint32_t(i));
+    const bool raised = s >= 0 && load_shared(&a.vals[s]) == v &&
+                        load_shared(&a.epoch[s]) == a.cur_epoch;
+    if (raised) atomicMax(reinterpret_cast<unsigned long long *>(&a.claim[s]), stamp);
+    if (fresh) {
+        store_map<RowT>(a, kids, i, s);
+        a.keys[s] = tag | kPublished;
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    const bool flag = raised && load_shared(&a.claim[s]) == stamp;
+    int pos;
+    const int total = block_prefix_any(flag, sums, pos);
+    const int kept = total < a.cap ? total : a.cap;
+    if (flag && pos < kept) {
+        src[pos] = i;
+        a.next_reward[pos] = reward;
+        a.next_depth[pos] = depth;
+        if (f.pool) {
+            key[pos] = v;
+            f.pool_val[f.pool_n + pos] = v;
+            f.pool_slot[f.pool_n + pos] = s;
+        }
+    }
+    __syncthreads();
+    const int ndst = f.pool ? f.pcap : kept, off = f.pool ? f.pool_n : 0;
+    if ((a.H * sizeof(RowT)) % 16 == 0)
+        copy_blocks(static_cast<const uint4 *>(kids), a.n, static_cast<uint4 *>(a.next), ndst, off,
+                    kept, int(a.H * sizeof(RowT) / 16), a.C, src);
+    else
+        copy_blocks(static_cast<const RowT *>(kids), a.n, static_cast<RowT *>(a.next), ndst, off,
+                    kept, a.H, a.C, src);
+    // a full pool or table ends the search: nothing is merged
+    const int nn = bad || total > a.cap ? 0 : total;
+    if (f.pool && i < nn) {
+        // the sorted place: new nodes of a larger value, or of the same one and a smaller id
+        const uint64_t mine = key[i];
+        int before = 0;
+        for (int q = 0; q < nn; ++q) before += key[q] > mine || (key[q] == mine && q < i);
+        f.new_keys[before] = mine;
+        f.new_ids[before] = uint32_t(f.pool_n + i);
+    }
+    if (i == 0) {
+        a.counts[3] = uint32_t(nn);
+        host->best = load_shared(a.best);
+        host->terminal = terminal;
+        host->overflow = bad;
+        host->survivors = uint32_t(total);
+    }
+}
+
+// Rows of blocks src_of[q] of a [C][n][H] buffer into blocks off + q of a [C][ndst][H] one.
+template <typename RowT>
+__global__ void __launch_bounds__(256) copy_kernel(const void *kids, int n, void *next, int nn,
+                                                   const int32_t *src_of, int C, int H, int ndst,
+                                                   int off) {
+    const size_t r = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (r >= size_t(C) * nn * H) return;
+    const int y = int(r % H);
+    const size_t cq = r / H;
+    const int q = int(cq % nn), c = int(cq / nn);
+    static_cast<RowT *>(next)[(size_t(c) * ndst + off + q) * H + y] =
+        static_cast<const RowT *>(kids)[(size_t(c) * n + src_of[q]) * H + y];
+}
+
+// The root: one wave.  The table is empty: the root takes its home slot, published at once.
+// Best-first also makes it node 0 of the pool and the only entry of the open list.
+template <typename RowT>
+__global__ void __launch_bounds__(64) root_kernel(SearchArgs a, BestFirstArgs f, const void *front) {
+    const int t = threadIdx.x;
+    const uint64_t h = map_hash<RowT>(front, 0, 1, a.C, a.H) & a.hash_mask;
+    const uint64_t s = h & a.mask;
+    RowT *dst = reinterpret_cast<RowT *>(static_cast<char *>(a.store) +
+                                         size_t(s) * a.C * a.H * sizeof(RowT));
+    for (int r = t; r < a.C * a.H; r += 64) {
+        const RowT row = static_cast<const RowT *>(front)[r];
+        dst[r] = row;
+        if (f.pool) {
+            const int c = r / a.H;
+            static_cast<RowT *>(f.pool)[size_t(c) * f.pcap * a.H + (r - c * a.H)] = row;
+        }
+    }
+    if (t < 3) a.counts[t] = 0u;
+    if (t != 0) return;
+    const uint64_t v = pack_value(0, 0);
+    a.keys[s] = (uint64_t(hash_tag(h)) << 32) | kPublished;
+    a.vals[s] = v;
+    *a.best = (uint64_t(0x80000000u) << 32) | 0xFFFFFFFFull;
+    a.next_reward[0] = 0;
+    a.next_depth[0] = 0;
+    if (f.pool) {
+        f.pool_reward[0] = 0;
+        f.pool_depth[0] = 0;
+        f.pool_val[0] = v;
+        f.pool_slot[0] = int64_t(s);
+        f.open_keys[0] = v;
+        f.open_ids[0] = 0u;
+        f.parents[0] = 0;
+    }
+}
+
+// ---------------------------------------------------------------------------------------
+// Batched best-first (av_search_config.best_first_k > 0).  Nodes live in a pool ([C][P][H]
+// rows plus reward, depth, packed (reward, -depth) value and table slot per node id); the
+// open list holds (value, id) pairs sorted by value descending, ties by id ascending.  An
+// iteration pops its first k entries, keeps those whose value is still their slot's value
+// (the others were beaten by a later copy of their state), expands them in id order with the
+// level kernels above, appends the survivors to the pool with the next ids, sorts them, and
+// merges them into the rest of the open list.
+
+// Pop: the first kp = min(K, m + nn) open ids, sorted ascending (bitonic, 512 slots), those
+// still alive compacted into parents[]; their number goes to the host.  nn: *new_n if given (the
+// level's new nodes, which the host does not know yet), else 0 (m counts all).  One workgroup of
+// 512 threads.
+__global__ void __launch_bounds__(512) bf_pop_kernel(const uint32_t *open_ids, int K, int m,
+                                                     const uint32_t *new_n,
                                                      const int64_t *pool_slot,
                                                      const uint64_t *pool_val,
                                                      const uint64_t *vals, int32_t *parents,
-                                                     uint32_t *n_par, uint32_t *counts) {
+                                                     SearchResult *host, uint32_t *counts) {
     __shared__ uint32_t ids[512];
-    if (threadIdx.x < 3) counts[threadIdx.x] = 0u;   // the level's counters, for what follows
+    const int kp = min(K, m + (new_n ? int(*new_n) : 0));
+    if (threadIdx.x < 3) counts[threadIdx.x] = 0u;   // the next level's counters
     __shared__ int sums[8];
     const int t = threadIdx.x;
     ids[t] = t < kp ? open_ids[t] : 0xFFFFFFFFu;
@@ -413,17 +585,28 @@ __global__ void __launch_bounds__(512) bf_pop_kernel(const uint32_t *open_ids, i
     int prefix;
     const int total = block_prefix_any(alive, sums, prefix);
     if (alive) parents[prefix] = int32_t(id);
-    if (t == 0) *n_par = uint32_t(total);
+    if (t == 0) host->parents = uint32_t(total);
 }
 
-__global__ void __launch_bounds__(256) bf_gather_meta(const int32_t *parents, int np,
-                                                      const int32_t *pool_reward,
-                                                      const int32_t *pool_depth,
-                                                      int32_t *front_reward, int32_t *front_depth) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= np) return;
-    front_reward[i] = pool_reward[parents[i]];
-    front_depth[i] = pool_depth[parents[i]];
+// The np parents' rows (V: 16 bytes or a row, `per` to a channel) from the pool [C][pcap][per]
+// into the frontier buffer [C][np][per], and their reward and depth.
+template <typename V>
+__global__ void __launch_bounds__(256) bf_gather_kernel(const V *pool, int pcap,
+                                                        const int32_t *parents, int np, int per,
+                                                        int C, V *front, const int32_t *pool_reward,
+                                                        const int32_t *pool_depth,
+                                                        int32_t *front_reward,
+                                                        int32_t *front_depth) {
+    const size_t t = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (t < size_t(np)) {
+        front_reward[t] = pool_reward[parents[t]];
+        front_depth[t] = pool_depth[parents[t]];
+    }
+    if (t >= size_t(C) * np * per) return;
+    const int k = int(t % per);
+    const size_t cq = t / per;
+    const int q = int(cq % np), c = int(cq / np);
+    front[t] = pool[(size_t(c) * pcap + parents[q]) * per + k];
 }
 
 // New nodes pool_n + q (q < nn) from survivor children src_of[q]: value and slot, and the
@@ -481,9 +664,11 @@ __global__ void __launch_bounds__(1024) bf_sort_kernel(uint64_t *keys, uint32_t 
 // Merge the old open list (m pairs) with the sorted new pairs (nn) into out: old entries
 // come before new ones of equal value (their ids are smaller).
 __global__ void __launch_bounds__(256) bf_merge_kernel(const uint64_t *ok, const uint32_t *oi, int m,
-                                                       const uint64_t *nk, const uint32_t *ni, int nn,
+                                                       const uint64_t *nk, const uint32_t *ni,
+                                                       int most, const uint32_t *new_n,
                                                        uint64_t *outk, uint32_t *outi) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int nn = new_n ? int(*new_n) : most;   // new pairs: at most `most`
     if (t < m) {
         const uint64_t key = ok[t];
         int lo = 0, hi = nn;                       // new entries with a larger value
@@ -558,7 +743,7 @@ hipError_t level_impl(const SearchArgs &a, const void *front, int nf, void *kids
         hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(256), 0, s, a.block_count, int(nb),
                            &a.counts[2]);
         hipLaunchKernelGGL(place_kernel, dim3(nb), dim3(256), 0, s, a, a.cap);
-    } else if (phase == 2) {
+    } else {
         if (nn > 0 && by16)
             hipLaunchKernelGGL(copy16_kernel, dim3(blocks_for(size_t(a.C) * nn * chunks)), dim3(256),
                                0, s, static_cast<const uint4 *>(kids), a.n,
@@ -570,8 +755,6 @@ hipError_t level_impl(const SearchArgs &a, const void *front, int nf, void *kids
             hipLaunchKernelGGL(copy_kernel<RowT>, dim3(blocks_for(size_t(a.C) * nn * a.H)), dim3(256),
                                0, s, kids, a.n, a.next, nn, a.src_of, a.C, a.H, a.next_n,
                                a.next_off);
-    } else {
-        hipLaunchKernelGGL(root_kernel<RowT>, dim3(1), dim3(64), 0, s, a, front);
     }
     return hipGetLastError();
 }
@@ -603,20 +786,61 @@ hipError_t launch_copy_rows(int row_bytes, const void *src, int nsrc, const int3
     return copy_rows<uint64_t>(src, nsrc, src_of, dst, ndst, off, n, C, H, s);
 }
 
-hipError_t launch_bf_pop(const uint32_t *open_ids, int kp, const int64_t *pool_slot,
-                         const uint64_t *pool_val, const uint64_t *vals, int32_t *parents,
-                         uint32_t *n_par, uint32_t *counts, hipStream_t s) {
-    hipLaunchKernelGGL(bf_pop_kernel, dim3(1), dim3(512), 0, s, open_ids, kp, pool_slot, pool_val,
-                       vals, parents, n_par, counts);
+hipError_t launch_root(const SearchArgs &a, const BestFirstArgs &f, int row_bytes,
+                       const void *front, hipStream_t s) {
+    if (row_bytes == 2)
+        hipLaunchKernelGGL(root_kernel<uint16_t>, dim3(1), dim3(64), 0, s, a, f, front);
+    else if (row_bytes == 4)
+        hipLaunchKernelGGL(root_kernel<uint32_t>, dim3(1), dim3(64), 0, s, a, f, front);
+    else
+        hipLaunchKernelGGL(root_kernel<uint64_t>, dim3(1), dim3(64), 0, s, a, f, front);
     return hipGetLastError();
 }
 
-hipError_t launch_bf_gather_meta(const int32_t *parents, int np, const int32_t *pool_reward,
-                                 const int32_t *pool_depth, int32_t *front_reward,
-                                 int32_t *front_depth, hipStream_t s) {
-    if (np <= 0) return hipSuccess;
-    hipLaunchKernelGGL(bf_gather_meta, dim3(blocks_for(size_t(np))), dim3(256), 0, s, parents, np,
-                       pool_reward, pool_depth, front_reward, front_depth);
+bool small_level(const SearchArgs &a, int row_bytes) {
+    return a.n <= kSmallLevel && size_t(a.n) * a.C * a.H * row_bytes <= kSmallLevelBytes;
+}
+
+hipError_t launch_small_level(const SearchArgs &a, const BestFirstArgs &f, int row_bytes,
+                              const void *kids, SearchResult *host, hipStream_t s) {
+    const dim3 block((a.n + 63) / 64 * 64);
+    if (row_bytes == 2)
+        hipLaunchKernelGGL(small_level_kernel<uint16_t>, dim3(1), block, 0, s, a, f, kids, host);
+    else if (row_bytes == 4)
+        hipLaunchKernelGGL(small_level_kernel<uint32_t>, dim3(1), block, 0, s, a, f, kids, host);
+    else
+        hipLaunchKernelGGL(small_level_kernel<uint64_t>, dim3(1), block, 0, s, a, f, kids, host);
+    return hipGetLastError();
+}
+
+hipError_t launch_bf_pop(const uint32_t *open_ids, int K, int m, const uint32_t *new_n,
+                         const int64_t *pool_slot, const uint64_t *pool_val, const uint64_t *vals,
+                         int32_t *parents, SearchResult *host, uint32_t *counts, hipStream_t s) {
+    hipLaunchKernelGGL(bf_pop_kernel, dim3(1), dim3(512), 0, s, open_ids, K, m, new_n, pool_slot,
+                       pool_val, vals, parents, host, counts);
+    return hipGetLastError();
+}
+
+hipError_t launch_bf_gather(int row_bytes, const BestFirstArgs &f, int np, void *front,
+                            int32_t *front_reward, int32_t *front_depth, int C, int H,
+                            hipStream_t s) {
+    const int bytes = H * row_bytes;
+    const int per = bytes % 16 == 0 ? bytes / 16 : H;
+    const dim3 grid(blocks_for(size_t(C) * np * per));      // C per >= 4: covers the np too
+#define AV_GATHER(V)                                                                          \
+    hipLaunchKernelGGL(bf_gather_kernel<V>, grid, dim3(256), 0, s,                            \
+                       static_cast<const V *>(f.pool), f.pcap, f.parents, np, per, C,         \
+                       static_cast<V *>(front), f.pool_reward, f.pool_depth, front_reward,    \
+                       front_depth)
+    if (bytes % 16 == 0)
+        AV_GATHER(uint4);
+    else if (row_bytes == 2)
+        AV_GATHER(uint16_t);
+    else if (row_bytes == 4)
+        AV_GATHER(uint32_t);
+    else
+        AV_GATHER(uint64_t);
+#undef AV_GATHER
     return hipGetLastError();
 }
 
@@ -633,11 +857,11 @@ hipError_t launch_bf_append(const int32_t *src_of, int nn, int pool_n, const uin
 }
 
 hipError_t launch_bf_merge(const uint64_t *ok, const uint32_t *oi, int m, const uint64_t *nk,
-                           const uint32_t *ni, int nn, uint64_t *outk, uint32_t *outi,
-                           hipStream_t s) {
+                           const uint32_t *ni, int nn, const uint32_t *new_n, uint64_t *outk,
+                           uint32_t *outi, hipStream_t s) {
     if (m + nn <= 0) return hipSuccess;
     hipLaunchKernelGGL(bf_merge_kernel, dim3(blocks_for(size_t(m) + nn)), dim3(256), 0, s, ok, oi, m,
-                       nk, ni, nn, outk, outi);
+                       nk, ni, nn, new_n, outk, outi);
     return hipGetLastError();
 }
 
