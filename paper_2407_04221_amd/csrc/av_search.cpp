@@ -273,6 +273,7 @@ av_status av_search_begin(av_search_t s, const uint8_t *root) {
         s->pool_n = 1;
         s->open_n = 1;
         s->npar = 1;                                      // the root
+        SEARCH_HIP(hipStreamSynchronize(s->stream));      // the caller's root is read
     }
     s->n_front = 1;
     s->level = 0;

@@ -74,13 +74,25 @@ __device__ inline uint64_t map_hash(const void *state, int i, int n, int C, int 
                 h = mix64(h ^ (uint64_t(q.z) | (uint64_t(q.w) << 32)));
             }
         } else {
+            // the last word's rows first, then four words at a time: their loads are in flight
+            // together (row by row a 13-row map's hash waited for every row)
             constexpr int per = 8 / int(sizeof(RowT));
-            for (int y0 = 0; y0 < H; y0 += per) {
-                uint64_t word = 0;
-                for (int k = 0; k < per && y0 + k < H; ++k)
-                    word |= uint64_t(blk[y0 + k]) << (8 * int(sizeof(RowT)) * k);
-                h = mix64(h ^ word);
+            const int whole = H / per;
+            uint64_t last = 0;
+#pragma unroll
+            for (int k = 0; k < per - 1; ++k)
+                if (whole * per + k < H)
+                    last |= uint64_t(blk[whole * per + k]) << (8 * int(sizeof(RowT)) * k);
+            for (int w0 = 0; w0 < whole; w0 += 4) {
+                uint64_t v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (w0 + u < whole) __builtin_memcpy(&v[u], blk + (w0 + u) * per, 8);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (w0 + u < whole) h = mix64(h ^ v[u]);
             }
+            if (whole * per < H) h = mix64(h ^ last);
         }
     }
     return h ? h : 1;
@@ -135,8 +147,20 @@ __device__ inline bool same_map(const void *kids, int n, int i, int j, const voi
     for (int c = 0; c < C; ++c) {
         const RowT *ra = a + (size_t(c) * n + i) * H;
         const RowT *rb = j >= 0 ? b + (size_t(c) * n + j) * H : b + size_t(c) * H;
-        for (int y = 0; y < H; ++y)
-            if (ra[y] != rb[y]) return false;
+        constexpr int per = 8 / int(sizeof(RowT));
+        uint64_t differ = 0;
+        int y = 0;
+#pragma unroll 4
+        for (; y + per <= H; y += per) {
+            uint64_t x, z;
+            __builtin_memcpy(&x, ra + y, 8);
+            __builtin_memcpy(&z, rb + y, 8);
+            differ |= x ^ z;
+        }
+#pragma unroll
+        for (int k = 0; k < per - 1; ++k)
+            if (y + k < H) differ |= uint64_t(ra[y + k] ^ rb[y + k]);
+        if (differ) return false;
     }
     return true;
 }
@@ -374,13 +398,26 @@ __device__ inline void copy_blocks(const V *src, int n, V *dst, int ndst, int of
     }
 }
 
+// The maps of children from[q] into the store entries of slots to[q], by the whole workgroup.
+template <typename V>
+__device__ inline void store_maps(const V *kids, int n, V *store, int per, int C, int taken,
+                                  const int32_t *from, const int64_t *to) {
+    const uint32_t map = uint32_t(C) * uint32_t(per), all = uint32_t(taken) * map;
+    for (uint32_t r = threadIdx.x; r < all; r += blockDim.x) {
+        const uint32_t q = r / map, in = r - q * map, c = in / uint32_t(per);
+        const uint32_t y = in - c * uint32_t(per);
+        store[size_t(to[q]) * map + in] = kids[(size_t(c) * n + from[q]) * per + y];
+    }
+}
+
 // A whole level of at most kSmallLevel children in one workgroup, one child per thread: post,
 // claim, flag, scan, place and copy of the survivors, with barriers where the kernels above end,
 // and with f.pool also the new nodes' pool entries and their sorted (value, id) list.  A level
 // this small is bound by the time between kernels, not by the work: the six kernels, a fill, two
 // copies to the host and a second synchronisation of a best-first iteration, which took nearly
 // all of its time, are one launch and one wait.  Measured (MI355X): best-first, 32 parents, 8000
-// visits of 13 x 11 maps 7716 -> 3904 us; level order, 200000 visits of 16 x 16 maps, four of
+// visits of 13 x 11 maps 7716 -> 3904 us (3455 with the taken maps stored by the whole
+// workgroup and a map's rows loaded together for its hash); level order, 200000 visits of 16 x 16 maps, four of
 // eight levels this small, 935 -> 588 us.  What other threads of the level
 // wrote (the table's value, epoch and claim words) is read past the first-level cache.
 template <typename RowT>
@@ -389,11 +426,12 @@ __global__ void __launch_bounds__(kSmallLevel) small_level_kernel(SearchArgs a, 
                                                                   SearchResult *host) {
     __shared__ uint64_t key[kSmallLevel];
     __shared__ int32_t src[kSmallLevel];
+    __shared__ int64_t slot[kSmallLevel];
     __shared__ int sums[kSmallLevel / 64];
-    __shared__ uint32_t terminal, bad;
+    __shared__ uint32_t terminal, bad, taken;
     const int i = threadIdx.x;
     const bool in = i < a.n;
-    if (i == 0) terminal = bad = 0u;
+    if (i == 0) terminal = bad = taken = 0u;
     __syncthreads();
 
     int32_t reward = 0, depth = 0;
@@ -431,6 +469,11 @@ __global__ void __launch_bounds__(kSmallLevel) small_level_kernel(SearchArgs a, 
             const uint64_t old = atomicMax(reinterpret_cast<unsigned long long *>(&a.vals[s]),
                                            static_cast<unsigned long long>(v));
             if (old < v) store_shared(&a.epoch[s], a.cur_epoch);
+            if (fresh) {
+                const uint32_t q = atomicAdd(&taken, 1u);
+                src[q] = i;
+                slot[q] = s;
+            }
         }
     }
     __builtin_amdgcn_s_waitcnt(0);
@@ -441,10 +484,15 @@ __global__ void __launch_bounds__(kSmallLevel) small_level_kernel(SearchArgs a, 
     const bool raised = s >= 0 && load_shared(&a.vals[s]) == v &&
                         load_shared(&a.epoch[s]) == a.cur_epoch;
     if (raised) atomicMax(reinterpret_cast<unsigned long long *>(&a.claim[s]), stamp);
-    if (fresh) {
-        store_map<RowT>(a, kids, i, s);
-        a.keys[s] = tag | kPublished;
-    }
+    if (fresh) a.keys[s] = tag | kPublished;
+    const bool by16 = (a.H * sizeof(RowT)) % 16 == 0;
+    const int per = by16 ? int(a.H * sizeof(RowT) / 16) : a.H;
+    if (by16)
+        store_maps(static_cast<const uint4 *>(kids), a.n, static_cast<uint4 *>(a.store), per, a.C,
+                   int(taken), src, slot);
+    else
+        store_maps(static_cast<const RowT *>(kids), a.n, static_cast<RowT *>(a.store), per, a.C,
+                   int(taken), src, slot);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     const bool flag = raised && load_shared(&a.claim[s]) == stamp;
@@ -463,12 +511,12 @@ __global__ void __launch_bounds__(kSmallLevel) small_level_kernel(SearchArgs a, 
     }
     __syncthreads();
     const int ndst = f.pool ? f.pcap : kept, off = f.pool ? f.pool_n : 0;
-    if ((a.H * sizeof(RowT)) % 16 == 0)
+    if (by16)
         copy_blocks(static_cast<const uint4 *>(kids), a.n, static_cast<uint4 *>(a.next), ndst, off,
-                    kept, int(a.H * sizeof(RowT) / 16), a.C, src);
+                    kept, per, a.C, src);
     else
         copy_blocks(static_cast<const RowT *>(kids), a.n, static_cast<RowT *>(a.next), ndst, off,
-                    kept, a.H, a.C, src);
+                    kept, per, a.C, src);
     // a full pool or table ends the search: nothing is merged
     const int nn = bad || total > a.cap ? 0 : total;
     if (f.pool && i < nn) {
