@@ -179,9 +179,11 @@ struct RowsArgs {
 // the other three help with the probe pass and the four-entry filter (each wave takes a
 // quarter of the anchor rows) and with matching the candidates (each wave takes every fourth
 // one, ORs its votes into the shared accumulators and adds its reward, rule count and voted
-// planes to three shared counters); wave 0 then writes the planes.  The waves meet at a
-// barrier after the force, after the probe, after the filter (when it runs) and after the
-// match (when there are candidates).
+// planes to three shared counters) and with writing the voted planes (each wave every fourth
+// one).  The waves meet at a barrier after the force, after the probe, after the filter (when it
+// runs), and after the match and the write (when there are two or more candidates).
+// A crowded step's recounts were wave 0's alone while three waves waited: 256 maps of 64 x 64, 12
+// channels, 32 rules of 5 x 5 planted on the first map, 100 steps, 2497 -> 1975 us once dealt.
 template <typename RowT, int RB, int kWaves>
 __global__ void __launch_bounds__(64 * kWaves) rows_step(StepArgs a, RowsArgs rp) {
     using ST = typename RowStore<RB>::T;
@@ -471,26 +473,26 @@ __global__ void __launch_bounds__(64 * kWaves) rows_step(StepArgs a, RowsArgs rp
                 }
             } while (false);
             if (shared && last) {
-                // the helper waves add their rewards and voted planes to the shared counters;
-                // wave 0 goes on with the totals (its own rewards stay in its lanes)
-                if (wv != 0) {
-                    if (wave_any(rsum != 0))
-                        for (int off = 32; off > 0; off >>= 1) rsum += __shfl_xor(rsum, off, 64);
-                    if (y == 0) {
-                        if (rsum != 0) atomicAdd(&lcnt[2], rsum);
-                        if (touched != 0) atomicOr(reinterpret_cast<unsigned *>(&lcnt[1]), touched);
-                    }
+                // the waves add their voted planes to the shared counters, the helpers their
+                // rewards too (wave 0's own stay in its lanes); all go on with the totals
+                if (wv != 0 && wave_any(rsum != 0))
+                    for (int off = 32; off > 0; off >>= 1) rsum += __shfl_xor(rsum, off, 64);
+                if (y == 0) {
+                    if (wv != 0 && rsum != 0) atomicAdd(&lcnt[2], rsum);
+                    if (touched != 0) atomicOr(reinterpret_cast<unsigned *>(&lcnt[1]), touched);
                 }
                 __syncthreads();
-                if (wv != 0) break;
-                nf = lcnt[0];
-                touched |= uint32_t(lcnt[1]);
-                if (y == 0) rsum += lcnt[2];
+                nf = __builtin_amdgcn_readfirstlane(lcnt[0]);
+                touched = uint32_t(__builtin_amdgcn_readfirstlane(lcnt[1]));
+                if (wv == 0 && y == 0) rsum += lcnt[2];
             }
             if (nf > 0 && (a.sequential || last)) {
                 // write the planes the batch's rules voted on; planes where some cell got
-                // votes of both signs are recounted exactly
-                for (uint32_t t = touched; t; t &= t - 1) {
+                // votes of both signs are recounted exactly.  Shared, wave w writes every nw-th
+                // voted plane from the w-th on: the recounts are most of a crowded step.
+                int q = 0;
+                for (uint32_t t = touched; t; t &= t - 1, ++q) {
+                    if (shared && (q & (nw - 1)) != wv) continue;
                     const int c = __builtin_ctz(t);
                     const RowT old = Pl[c * hp + ry], pl = Vp[c * hp + ry], mi = Vm[c * hp + ry];
                     RowT nv = (old | pl) & ~mi;
@@ -505,6 +507,7 @@ __global__ void __launch_bounds__(64 * kWaves) rows_step(StepArgs a, RowsArgs rp
                 touched = 0;
                 nf = 0;
             }
+            if (shared && last) __syncthreads();   // every plane is written, the counters are read
             if (last) break;
         }
         if (wv != 0) continue;                    // helper waves: the rest is wave 0's
