@@ -30,10 +30,11 @@
 // 15.8 -> 1.04 ms.
 //
 // LDS (32-bit rows):
-//   P    [C+1][PR]     the map and the force plane (channel C); PR = HR + ph - 1 rounded up to
-//                      4 rows (ph: the largest pattern's rows), so a lane reads row y + i of
-//                      any pattern entry without a bounds test (rows H .. PR - 1 stay zero)
-//   M    [R+5][PR]     match planes, row y at ph - 1 + y: the zero rows above let a vote read
+//   P    [C+1][PR]     the map and the force plane (channel C); PR = HR + PAD rounded up to 4
+//                      rows (PAD: the largest pattern's rows - 1, and at least the 1 of the two-row
+//                      built-in moves), so a lane reads row y + i of any pattern entry without a
+//                      bounds test (rows H .. PR - 1 stay zero)
+//   M    [R+5][PR]     match planes, row y at PAD + y: the zero rows above let a vote read
 //                      match row y - i without a test (plane R + 4: zeros, read by votes past the
 //                      end of a list); MV [R+4][PR] the same after control (CTL; else M)
 //   DR   [HR]          anchors to test, Q [R][HR] a window's matches
@@ -106,10 +107,15 @@ constexpr int kMaxChan = 32;            // channels with a vote list
 constexpr int kKeyCells = 8;            // cells of a row one lane holds keys for
 constexpr int kShortLaunch = 16;        // launches of fewer steps read the lists from memory
 
+// Rows of the tallest pattern beyond its first, the built-in moves (two rows) among the patterns:
+// with loaded patterns of one row, too, the moves' votes read the match row above a cell's.
+__host__ __device__ constexpr int group_pad(int max_pat_h) {
+    return max_pat_h > 2 ? max_pat_h - 1 : 1;
+}
 // Words per plane row block: HR rows plus the pattern rows hanging below the last one,
 // rounded up to 4 (16-byte aligned table after the planes).
 __host__ __device__ constexpr int group_plane_words(int rows, int max_pat_h) {
-    return (rows + max_pat_h - 1 + 3) & ~3;
+    return (rows + group_pad(max_pat_h) + 3) & ~3;
 }
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __host__ __device__ constexpr int key_stride(int W) { return W | 1; }
@@ -278,7 +284,7 @@ __global__ void __launch_bounds__(64, WAVES) group_step(StepArgs a) {
     const int NC = SEQ ? C1 : C;
     // pattern rows beyond a lane's row: plane rows y + i and match rows y - i, i <= PAD, are
     // read without a bounds test
-    const int PAD = a.max_pat_h - 1;
+    const int PAD = group_pad(a.max_pat_h);
     const int PR = group_plane_words(HR, a.max_pat_h), MS = PR;
     const int s = a.per_env ? b : 0;
     const int nl = Rt - kMoveRules;               // loaded rules
@@ -538,7 +544,7 @@ __global__ void __launch_bounds__(64, WAVES) group_step(StepArgs a) {
             }
             Dd[h] = t[h];
         }
-        for (int i = 1; i <= PAD; ++i) {
+        for (int i = 1; i < a.max_pat_h; ++i) {
             next_rows<RPL>(t, t, y);
 #pragma unroll
             for (int h = 0; h < RPL; ++h) Dd[h] |= t[h];
@@ -883,7 +889,7 @@ __global__ void __launch_bounds__(64, WAVES) group_step(StepArgs a) {
 #pragma unroll
         for (int h = 0; h < RPL; ++h)
             rows |= uint32_t(__builtin_amdgcn_ballot_w64(fm[h] != 0u) & 0xFFFFull) << (kHq * h);
-        const int last = min(31 - __builtin_clz(rows) + PAD, HR - 1);
+        const int last = min(31 - __builtin_clz(rows) + a.max_pat_h - 1, HR - 1);
         int from = 0, past = HR;                  // the rows written
         if (!window(rows | (1u << last))) {
             from = r0;
@@ -1320,7 +1326,7 @@ struct EntryMerger {
 void compile_group_tables(const GenericProgram &p, int H, int W, int C, int lists, int max_pat_h,
                           std::vector<uint32_t> &tab, int &stride, int &entry_words) {
     const int Rt = p.rules_per_set, C1 = C + 1;
-    const int PR = group_plane_words(group_rows(H), max_pat_h), PAD = max_pat_h - 1;
+    const int PR = group_plane_words(group_rows(H), max_pat_h), PAD = group_pad(max_pat_h);
     const int head = group_head_words(Rt, lists);
     EntryMerger em(H, W, C, PR);
     std::vector<uint32_t> merged;                 // every rule's entries, one after another

@@ -64,3 +64,38 @@ def test_one_wave_kernel_matches_oracle(case, mode, order):
         np.testing.assert_array_equal(r, want_r)
         np.testing.assert_array_equal(d, want_d)
         np.testing.assert_array_equal(final, want_m[-1])
+
+
+@pytest.mark.parametrize("mode,order", MODES, ids=[f"{m}-{o}" for m, o in MODES])
+@pytest.mark.parametrize("H,W,B,variant", [(16, 16, 19, "planted"), (16, 9, 19, "dense"),
+                                           (32, 32, 19, "planted"), (32, 17, 19, "dense"),
+                                           (31, 32, 19, "planted"), (16, 12, 2100, "planted"),
+                                           (32, 11, 2100, "planted")])
+def test_one_row_patterns_match_oracle(H, W, B, variant, mode, order):
+    """Patterns of one row, where only the two-row built-in moves need a row above a match
+    plane, on maps that fill the planes' 16 or 32 rows, with players moving on the last row."""
+    require_gpu()
+    if B > 100 and order == "rowmajor":
+        pytest.skip("the large batches run one order")
+    w = wl(f"row{H}", 40 + H + W, H=H, W=W, B=B, R=6, shapes=((1, 1), (1, 2), (1, 3)),
+           T=30 if B < 100 else 18)
+    say(f"[one-row patterns] {H}x{W} B={B} {variant} {mode} {order}")
+    maps = inputs.make_maps(w, 3)
+    g = np.random.default_rng(H * W)
+    last = g.random((B, W)) < 0.3                      # more players, on the last row
+    maps[:, :, H - 1] = np.where(last[:, None], np.arange(w.C)[:, None] == inputs.PLAYER,
+                                 maps[:, :, H - 1])
+    rules = inputs.make_rules(w, 3, variant, init_maps=maps)
+    actions = inputs.make_actions(w, 3)
+    control = None
+    if order:
+        limit, inhibit = random_control(np.random.default_rng(5), w.B, w.R, p_inh=0.1, kmax=9)
+        control = (limit, inhibit, int(order == "random"), 77)
+    want_m, want_r, want_d = oracle.run(w, maps, rules, actions, nthreads=8,
+                                        rule_mode=int(mode == "sequential"), control=control)
+    for chunk in (w.T, 3):
+        _, final, r, d, _ = gpu_run(w, maps, rules, actions, mode="step_n", chunk=chunk,
+                                    rule_mode=mode, control=control)
+        np.testing.assert_array_equal(r, want_r)
+        np.testing.assert_array_equal(d, want_d)
+        np.testing.assert_array_equal(final, want_m[-1])
