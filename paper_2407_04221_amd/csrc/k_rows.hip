@@ -179,17 +179,27 @@ struct RowsArgs {
 // the other three help with the probe pass and the four-entry filter (each wave takes a
 // quarter of the anchor rows) and with matching the candidates (each wave takes every fourth
 // one, ORs its votes into the shared accumulators and adds its reward, rule count and voted
-// planes to three shared counters) and with writing the voted planes (each wave every fourth
-// one).  The waves meet at a barrier after the force, after the probe, after the filter (when it
-// runs), and after the match and the write (when there are two or more candidates).
-// A crowded step's recounts were wave 0's alone while three waves waited: 256 maps of 64 x 64, 12
-// channels, 32 rules of 5 x 5 planted on the first map, 100 steps, 2497 -> 1975 us once dealt.
+// planes to three shared counters) and with writing the voted planes (wave w those of channels
+// w, w + 4, ...).  The waves meet at a barrier after the force, after the probe, after the filter
+// (when it runs), after the match (when there are two or more candidates) and after the write
+// (when one of those fired).
+//
+// A crowded step's recounts were wave 0's alone while three waves waited.  Dealing the planes out
+// put the voted planes and the fired rules' number in scalar registers of every wave, and what
+// that spilled cost every step, until the form without sequential order (which has no helpers)
+// dropped that order's registers.  100 steps, planes written by wave 0 / dealt, spilling / as it
+// is, us: 256 maps of 64 x 64, 12 channels, 32 rules of 5 x 5, planted on the first map 2460 /
+// 1933 / 1834, random 277 / 281 / 267, dense 314 / 324 / 309; 64 maps of 48 x 40, 6 channels, 8
+// rules of 3 x 3, planted 876 / 907 / 868, random 239 / 247 / 232, dense 5640 / 2668 / 2552; 256
+// maps of 64 x 32 (4-byte rows), 16 rules of 3 x 3, planted 1071 / 1073 / 1044, random 234 / 250 /
+// 239.
 template <typename RowT, int RB, int kWaves>
 __global__ void __launch_bounds__(64 * kWaves) rows_step(StepArgs a, RowsArgs rp) {
     using ST = typename RowStore<RB>::T;
     extern __shared__ __align__(16) unsigned char lds[];
     const int Rt = rp.rules;
     constexpr int nw = kWaves;
+    const bool seq = nw == 1 && a.sequential;     // helper waves: parallel rule order only
     const int y = int(threadIdx.x & 63u);
     const int wv = nw == 1 ? 0 : __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int b = int(blockIdx.x);
@@ -286,16 +296,17 @@ __global__ void __launch_bounds__(64 * kWaves) rows_step(StepArgs a, RowsArgs rp
             else if (act == 4) f = P[ry] >> 1;
             if (row) F[y] = f;
         }
-        if (nw > 1 && y < 3) lcnt[y] = 0;
         }
         if (nw > 1) __syncthreads();             // the map and this step's force plane are set
+        // the counters: every wave has read the step before's, and adds behind the probe's barrier
+        if (nw > 1 && wv == 1 && y < 3) lcnt[y] = 0;
         int rsum = 0, nf = 0;
         uint32_t touched = 0;   // planes that received votes in the current batch
         // The rules to visit: in sequential order every rule, one batch each (each matches the
         // map the rules before it left); in parallel order the candidates, one batch: rules
         // whose two probes hold together at some anchor (lane r tests rule r).
         uint64_t todo = all_rules;
-        if (!a.sequential) {
+        if (!seq) {
             RowT hit = 0;
             for (int yy = y0; yy < y1; ++yy) {
                 const RowT t = ((Pl[pa[0] + yy] >> pj[0]) ^ pinv[0]) &
@@ -315,7 +326,7 @@ __global__ void __launch_bounds__(64 * kWaves) rows_step(StepArgs a, RowsArgs rp
                     todo |= uint64_t(tslot[2 * w]) | (uint64_t(tslot[2 * w + 1]) << 32);
             }
         }
-        if (!a.sequential) {
+        if (!seq) {
             if (__popcll(todo) > 2) {
                 // many candidates (crowded maps): filter them with four entries at once
                 RowT hit = 0;
@@ -483,16 +494,14 @@ __global__ void __launch_bounds__(64 * kWaves) rows_step(StepArgs a, RowsArgs rp
                 }
                 __syncthreads();
                 nf = __builtin_amdgcn_readfirstlane(lcnt[0]);
-                touched = uint32_t(__builtin_amdgcn_readfirstlane(lcnt[1]));
+                touched = uint32_t(__builtin_amdgcn_readfirstlane(lcnt[1])) & (0x11111111u << wv);
                 if (wv == 0 && y == 0) rsum += lcnt[2];
             }
-            if (nf > 0 && (a.sequential || last)) {
+            if (nf > 0 && (seq || last)) {
                 // write the planes the batch's rules voted on; planes where some cell got
-                // votes of both signs are recounted exactly.  Shared, wave w writes every nw-th
-                // voted plane from the w-th on: the recounts are most of a crowded step.
-                int q = 0;
-                for (uint32_t t = touched; t; t &= t - 1, ++q) {
-                    if (shared && (q & (nw - 1)) != wv) continue;
+                // votes of both signs are recounted exactly: most of a crowded step.  (Shared,
+                // `touched` is the wave's part of them, and every wave comes here or none does.)
+                for (uint32_t t = touched; t; t &= t - 1) {
                     const int c = __builtin_ctz(t);
                     const RowT old = Pl[c * hp + ry], pl = Vp[c * hp + ry], mi = Vm[c * hp + ry];
                     RowT nv = (old | pl) & ~mi;
@@ -504,10 +513,10 @@ __global__ void __launch_bounds__(64 * kWaves) rows_step(StepArgs a, RowsArgs rp
                         Vm[c * hp + y] = 0;
                     }
                 }
+                if (shared && last) __syncthreads();
                 touched = 0;
                 nf = 0;
             }
-            if (shared && last) __syncthreads();   // every plane is written, the counters are read
             if (last) break;
         }
         if (wv != 0) continue;                    // helper waves: the rest is wave 0's

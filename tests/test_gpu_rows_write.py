@@ -1,6 +1,7 @@
 """The rows engine's tall maps (four waves an environment) against the oracle where the voted
 planes are dealt to the waves: fewer planes than waves up to four times as many, rows at and next
-to 33 and 64, 4- and 8-byte rows, resets, launches of one step and of many."""
+to 33 and 64, 4- and 8-byte rows, resets, launches of one step and of many; random rules, whose
+steps share a match in which no rule fires."""
 import numpy as np
 import pytest
 
@@ -11,7 +12,8 @@ from paper_2407_04221_amd import inputs
 pytestmark = pytest.mark.gpu
 
 CASES = [(33, 31, 4, 3, "dense"), (64, 64, 18, 24, "dense"), (63, 33, 12, 20, "planted"),
-         (34, 9, 5, 9, "dense"), (48, 32, 8, 16, "planted")]
+         (34, 9, 5, 9, "dense"), (48, 32, 8, 16, "planted"),
+         (50, 30, 6, 24, "literal"), (64, 64, 8, 24, "literal")]
 
 
 @pytest.mark.parametrize("H,W,C,R,variant", CASES)
