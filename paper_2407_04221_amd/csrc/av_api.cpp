@@ -167,6 +167,7 @@ int entry_rank(int c, int want, int C) {
     else ch = 4;
     return (want ? 0 : 8) + ch;
 }
+constexpr int kEntryRanks = 16;
 
 void compile_generic(const std::vector<std::vector<HostRule>> &sets, int C, bool force_votes,
                      GenericProgram &p) {
@@ -177,38 +178,44 @@ void compile_generic(const std::vector<std::vector<HostRule>> &sets, int C, bool
     std::vector<std::vector<uint32_t>> match(sets.size()), vote(sets.size()), rvote(sets.size());
     p.hdr.assign(size_t(p.sets) * p.rules_per_set, RuleHdr{});
     p.votes.assign(size_t(p.sets) * C1, VoteList{});
+    std::vector<std::pair<int, uint32_t>> ents;   // a rule's input entries and their ranks
+    std::vector<std::vector<uint32_t>> per_ch(C1);
     for (size_t s = 0; s < sets.size(); ++s) {
-        std::vector<std::vector<uint32_t>> per_ch(C1);
+        for (auto &v : per_ch) v.clear();
         for (int r = 0; r < p.rules_per_set; ++r) {
             const HostRule &hr = sets[s][r];
             RuleHdr &h = p.hdr[s * p.rules_per_set + r];
             h.n = hr.n; h.m = hr.m; h.reward = hr.reward;
             h.match_off = int(match[s].size());
-            std::vector<std::pair<int, uint32_t>> ents;
-            for (int c = 0; c < C1; ++c)
-                for (int i = 0; i < hr.n; ++i)
-                    for (int j = 0; j < hr.m; ++j) {
-                        const int w = hr.at(hr.in, c, i, j);
-                        if (w >= 0) ents.push_back({entry_rank(c, w, C), pack_match(c, i, j, w)});
-                        const int k = kout(w, hr.at(hr.out, c, i, j));
-                        if (k) per_ch[c].push_back(pack_vote(r, i, j, k > 0));
-                    }
             h.vote_off = int(rvote[s].size());
-            for (int c = 0; c < (force_votes ? C1 : C); ++c)
+            h.pad = 0;                    // bit c: the rule casts a rule-major vote on channel c
+            ents.clear();
+            int first[kEntryRanks + 1] = {};      // of each rank, then where its next entry goes
+            const int8_t *in = hr.in.data(), *out = hr.out.data();
+            for (int c = 0; c < C1; ++c) {
+                const bool counts = c < C || force_votes;
                 for (int i = 0; i < hr.n; ++i)
                     for (int j = 0; j < hr.m; ++j) {
-                        const int k = kout(hr.at(hr.in, c, i, j), hr.at(hr.out, c, i, j));
-                        if (k) rvote[s].push_back(pack_vote(c, i, j, k > 0));
+                        const int w = *in++, k = kout(w, *out++);
+                        if (w >= 0) {
+                            const int rank = entry_rank(c, w, C);
+                            ents.push_back({rank, pack_match(c, i, j, w)});
+                            ++first[rank + 1];
+                        }
+                        if (!k) continue;
+                        per_ch[c].push_back(pack_vote(r, i, j, k > 0));
+                        if (!counts) continue;
+                        rvote[s].push_back(pack_vote(c, i, j, k > 0));
+                        h.pad |= int32_t(1u << c);
                     }
+            }
             h.vote_cnt = int(rvote[s].size()) - h.vote_off;
-            h.pad = 0;                    // bit c: the rule casts a rule-major vote on channel c
-            for (int e = h.vote_off; e < int(rvote[s].size()); ++e)
-                if ((rvote[s][e] & 255u) < 32u) h.pad |= int32_t(1u << (rvote[s][e] & 255u));
             if (hr.reward != 0) p.any_reward = 1;
-            std::stable_sort(ents.begin(), ents.end(),
-                             [](auto &a, auto &b) { return a.first < b.first; });
-            for (auto &e : ents) match[s].push_back(e.second);
-            h.match_cnt = int(match[s].size()) - h.match_off;
+            // by rank, entries of one rank in the order above
+            for (int q = 0; q < kEntryRanks; ++q) first[q + 1] += first[q];
+            match[s].resize(match[s].size() + ents.size());
+            for (auto &e : ents) match[s][size_t(h.match_off + first[e.first]++)] = e.second;
+            h.match_cnt = int(ents.size());
         }
         for (int c = 0; c < C1; ++c) {
             p.votes[s * C1 + c] = VoteList{int(vote[s].size()), int(per_ch[c].size())};

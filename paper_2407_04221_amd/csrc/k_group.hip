@@ -76,6 +76,7 @@
 // `cap` keys at or above it, found bit by bit from the top (one ballot per held key and bit; keys
 // never tie).
 #include <algorithm>
+#include <cstring>
 #include <type_traits>
 
 #include "av_internal.h"
@@ -1294,6 +1295,7 @@ struct EntryMerger {
     int H, W, C, PR;
     std::vector<int32_t> place;                   // of (c, i, block) in out, -1
     std::vector<std::pair<float, uint32_t>> out;  // share of a typical map's cells passed, entry
+    std::vector<uint64_t> keys;                   // the same in order: share's bits, entry
 
     EntryMerger(int H_, int W_, int C_, int PR_)
         : H(H_), W(W_), C(C_), PR(PR_), place(size_t(C_ + 1) * kMaxPat * 2, -1) {}
@@ -1318,8 +1320,15 @@ struct EntryMerger {
         }
         for (int e = 0; e < cnt; ++e)
             place[((ent[e] & 255u) * kMaxPat + ((ent[e] >> 8) & 255u)) * 2 + (((ent[e] >> 16) & 255u) >> 3)] = -1;
-        // (equal ones by place, so that the order is one for every host)
-        std::sort(out.begin(), out.end());
+        // (equal ones by place, so that the order is one for every host; a share's bits order as it
+        // does, being positive)
+        keys.clear();
+        for (const auto &o : out) {
+            uint32_t share;
+            std::memcpy(&share, &o.first, 4);
+            keys.push_back((uint64_t(share) << 32) | o.second);
+        }
+        std::sort(keys.begin(), keys.end());
     }
 };
 
@@ -1338,8 +1347,8 @@ void compile_group_tables(const GenericProgram &p, int H, int W, int C, int list
         for (int r = kMoveRules; r < Rt; ++r) {
             const RuleHdr &h = p.hdr[size_t(s) * Rt + r];
             em.merge(p.match.data() + size_t(s) * p.match_stride + h.match_off, h.match_cnt);
-            for (const auto &o : em.out) merged.push_back(o.second);
-            counts.push_back(int32_t(em.out.size()));
+            for (const uint64_t key : em.keys) merged.push_back(uint32_t(key));
+            counts.push_back(int32_t(em.keys.size()));
         }
         size_t votes = 0;
         for (int c = 0; c < lists; ++c) votes += size_t(p.votes[size_t(s) * C1 + c].cnt);
