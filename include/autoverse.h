@@ -93,12 +93,9 @@ typedef enum {
                                environment's cycles and deals environments to workgroups so that
                                the slowest ones do not share a SIMD (results never depend on
                                the order; not while the stream is captured).  Needs parallel
-                               rule order, H, W <= 32,
-                               (max_rules + 4) x max_pat_h x max_pat_w <= 254 and, within 64 KiB of LDS, C + 1 planes
-                               and R + 4 match planes of HR + max_pat_h - 1 rows (rounded up to
-                               4), 3 C rows of HR, 12 words per rule plus 12, and C (R + 6)
-                               words, 4 bytes each (HR = 16, or 32 on maps of 17 to 32 rows);
-                               no rule application control */
+                               rule order, H, W <= 32, max_rules <= 60 and
+                               (max_rules + 4) x max_pat_h x max_pat_w <= 254 (its working set
+                               is then at most 33 KiB of LDS); no rule application control */
 } av_engine;
 
 /* Order in which the rules of one step are applied. */

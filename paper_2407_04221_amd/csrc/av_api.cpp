@@ -445,8 +445,7 @@ av_status av_create_batch(const av_config *cfg, av_batch_t *out) {
                                          c.max_pat_h, c.max_pat_w);
     if (c.engine == AV_ENGINE_GROUP && !group_ok)
         return fail(AV_EINVAL, "the group engine needs parallel rule order, H, W <= 32, "
-                    "(max_rules + 4) x max_pat_h x max_pat_w <= 254 and a working set within "
-                    "64 KiB of LDS");
+                    "max_rules <= 60 and (max_rules + 4) x max_pat_h x max_pat_w <= 254");
     const bool rows_ok = rows_eligible(c.height, c.width, c.channels, c.max_rules + kMoveRules);
     if (c.engine == AV_ENGINE_ROWS && !rows_ok)
         return fail(AV_EINVAL, "the rows engine needs at most 60 rules and %zu bytes of LDS (limit %d)",

@@ -283,8 +283,8 @@ bool rows_eligible(int H, int W, int C, int rules_per_set);
 hipError_t launch_rows_step(const StepArgs &a, const uint32_t *words, int set_words, int rules,
                             hipStream_t s);
 
-// The group engine (k_group.hip): one environment per wave, its rules dealt to 2 or 4 groups
-// of lanes; parallel rule order, no rule application control.
+// The group engine (k_group.hip): one environment per wave, eight lanes per rule; parallel rule
+// order, no rule application control.
 bool group_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int max_pat_w);
 // Sequential rule order or rule application control (the wave engine's batches) on the same kernel,
 // maps of up to 32 x 32; launch_wave_step takes it when the program has its tables.

@@ -1253,25 +1253,17 @@ size_t group_base_bytes(int H, int W, int C, int rules_per_set, int max_pat_h, b
 
 }  // namespace
 
-// The LDS set that bounds which batches the engine takes, as documented (with at most 64 rules and
-// 32 channels the kernel's own is never over 64 KiB).
-static size_t group_lds_bytes(int H, int C, int rules_per_set, int max_pat_h) {
-    const int HR = group_rows(H), PR = group_plane_words(HR, max_pat_h);
-    return sizeof(uint32_t) * (size_t(C + 1) * PR + size_t(rules_per_set) * PR +
-                               size_t(3) * C * HR + size_t(rules_per_set + 1) * kProbeWords +
-                               size_t(C) * (rules_per_set + 2));
-}
-
 bool group_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int max_pat_w) {
     if (H > 32 || W > 32) return false;
     // every vote a cell-channel gets comes from a distinct (rule, pattern cell): the 8-bit
     // counts of the exact write hold them (plus the old value) when there are at most 255
     if (long(rules_per_set) * max_pat_h * max_pat_w > 254) return false;
     // (rule masks are 64-bit; merged entries address rows of the stored and force planes in 12
-    // bits)
+    // bits: at most 1536 within these limits, and the LDS set at most 33 KiB)
     return rules_per_set <= 64 && C <= kMaxChan &&
            (C + 1) * group_plane_words(group_rows(H), max_pat_h) <= kMaxEntryOffset + 1 &&
-           group_lds_bytes(H, C, rules_per_set, max_pat_h) <= size_t(kLdsBudget);
+           group_base_bytes(H, W, C, rules_per_set, max_pat_h, false, false, false) <=
+               size_t(kLdsBudget);
 }
 
 bool group_mode_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int max_pat_w,
