@@ -228,8 +228,8 @@ def test_best_first_force_pays_skips_dominated_nodes():
 
 @pytest.mark.parametrize("name,k", [("c4", 204), ("c4", 205), ("c2", 52), ("c5", 300)])
 def test_best_first_level_sizes(name, k):
-    """Levels of up to 1024 children and 512 KiB of maps are one workgroup's: 1020 and 1025
-    children, and maps whose bytes set the line, with iterations on both sides of it."""
+    """Levels of up to 1024 children are one workgroup's: iterations of 1020 and of 1025 children,
+    and small ones of other maps."""
     require_gpu()
     wl = inputs.WORKLOADS[name].with_(B=1)
     say(f"[best-first level sizes] {name} k={k}")
@@ -237,3 +237,44 @@ def test_best_first_level_sizes(name, k):
     budget = 5000 if name == "c4" else 1500
     last = compare_best_first(wl, maps[0], one_set(rules), budget, 12, k)
     assert last["visited"] > 0
+
+
+def level_sizes(wl, root, rules, budget, levels, k):
+    """The oracle's children per level or iteration."""
+    if k:
+        o = osearch.BestFirst(wl.H, wl.W, wl.C, rules, wl.L, k=k)
+    else:
+        o = osearch.Search(wl.H, wl.W, wl.C, rules, wl.L, max_frontier=1 << 12)
+    o.begin(root)
+    out = []
+    for _ in range(levels):
+        info = o.expand(budget - o.visited)
+        out.append(info["children"])
+        if info["frontier"] == 0 or info["visited"] >= budget:
+            break
+    return out
+
+
+@pytest.mark.parametrize("H,W,C,k,over", [
+    (64, 64, 16, 12, False), (64, 64, 16, 13, True), (32, 32, 8, 102, False), (32, 32, 8, 103, True),
+    (64, 64, 12, 60, True), (63, 64, 12, 60, True), (31, 20, 31, 60, True), (9, 17, 31, 93, False),
+    (64, 64, 12, 0, True), (63, 64, 12, 0, True), (31, 20, 31, 0, True)])
+def test_levels_on_both_sides_of_the_byte_line(H, W, C, k, over):
+    """Levels of up to 512 KiB of maps are one workgroup's: searches whose levels pass that line
+    (or end one step of k below it), in best-first and (k = 0) level order, with channels of whole
+    16-byte words and of others."""
+    require_gpu()
+    wl = inputs.Workload("lv", 90, B=1, H=H, W=W, C=C, R=6, shapes=((1, 2), (2, 1), (2, 2)),
+                         p_dc=0.5, per_env=False, T=1, L=30)
+    say(f"[search byte line] {H}x{W} C={C} k={k}")
+    maps, rules, _ = inputs.make_all(wl, 1, "dense")
+    rules = one_set(rules)
+    budget, levels = 25 * max(k, 30), 12
+    line = 512 * 1024 // (C * H * (4 if W <= 32 else 8))
+    sizes = level_sizes(wl, maps[0], rules, budget, levels, k)
+    assert (max(sizes) > line) == over and min(sizes) <= line, (sizes, line)
+    if k:
+        assert max(sizes) == 5 * k
+        compare_best_first(wl, maps[0], rules, budget, levels, k)
+    else:
+        compare(wl, maps[0], rules, budget, levels)
