@@ -467,11 +467,12 @@ av_status av_create_batch(const av_config *cfg, av_batch_t *out) {
     if (c.engine != AV_ENGINE_AUTO) b->engine = c.engine;
     else if (lane16_ok) b->engine = AV_ENGINE_LANE16;
     // measured on MI355X: per-environment rule sets in parallel order run fastest on the group
-    // engine (16 x 16, 8 rules: 1.5 / 5.0 / 26 us per step with literal / planted / dense
-    // rules against the wave engine's 2.7 / 4.5 / 69; 32 x 32, 16 rules: 11.8 / 24.7 / 113
-    // against 17.6 / 31.0 / 228), otherwise on the wave engine (its rule groups match many
+    // engine (1024 of 16 x 16, 8 rules: 0.78 / 1.66 / 8.9 us per step with literal / planted /
+    // dense rules against the wave engine's 2.6 / 4.4 / 68; 4096 of 32 x 32, 16 rules: 6.2 / 12.3
+    // / 35 against 17.3 / 30.9 / 230), otherwise on the wave engine (its rule groups match many
     // rules of a crowded environment at once); shared sets the lane16 engine cannot take run
-    // on rows (64 x 64, 32 rules: 3.2 against the wave engine's 7.7 us per step)
+    // on rows (256 of 64 x 64, 32 rules: 2.4 / 17.4 / 2.9 against the wave engine's 4.9 / 16.3 /
+    // 5.0)
     else if (c.per_env_rules && group_ok) b->engine = AV_ENGINE_GROUP;
     else if (c.per_env_rules && wave_ok) b->engine = AV_ENGINE_WAVE;
     else if (rows_ok) b->engine = AV_ENGINE_ROWS;

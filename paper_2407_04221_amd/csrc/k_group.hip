@@ -20,14 +20,17 @@
 //     hold an anchor are finished, dealt to the octets as they come up.
 // Within a launch only: a launch's first step, and a step after a reset, tests every anchor.
 //
-// Measured (MI355X, one rule set per environment, 100 steps, against the form that tested every
-// anchor of every step with 16 lanes per rule and OR-ed votes before counting them): 1024 maps of
-// 16 x 16 with 8 rules planted on the first map 260 -> 200 us, with dense rules 24.6 -> 9.0 us per
-// step; 4096 of 32 x 32 with 16 rules planted 1632 -> 1239 us, dense 86 -> 42 us per step, random
-// rules 7.7 -> 6.6; one step of those with its observation 42.9 -> 32.7 us.  Against k_wave.hip's
-// several waves per environment: 777 maps of 23 x 19, sequential order, 50 steps 1760 -> 805 us;
-// 1024 of 32 x 32 with every rule capped at a random site and inhibiting the next, 50 steps
-// 15.8 -> 1.04 ms.
+// Measured (MI355X, one rule set per environment, us per step in long launches, against the form
+// that tested every anchor of every step with 16 lanes per rule and OR-ed votes before counting
+// them): 1024 maps of 16 x 16, 8 rules, random / planted on the first map / dense 0.83 / 2.34 / 24.4
+// -> 0.78 / 1.66 / 8.9; 4096 of 32 x 32, 16 rules 7.3 / 14.1 / 67.6 -> 6.2 / 11.7 / 35.3; one step of
+// those with its observation 41.7 -> 33.0.  Against k_wave.hip's several waves per environment: at
+// launch_wave_step, which takes this kernel for sequential order and control.  A one-wave kernel of
+// their own, which tested every anchor, was ahead of these modes with few rules that seldom fire
+// (50 sequential steps of 777 maps of 23 x 19, 7 rules, random / planted / dense 327 / 545 / 1940 us
+// against 362 / 656 / 1406 here) and behind with more (1024 of 32 x 32, 16 rules 113 / 406 / 5662
+// against 81 / 282 / 5404; every rule capped at a random site and inhibiting the next 1813 against
+// 1061).
 //
 // LDS (32-bit rows):
 //   P    [C+1][PR]     the map and the force plane (channel C); PR = HR + PAD rounded up to 4
@@ -1293,7 +1296,8 @@ struct EntryMerger {
         : H(H_), W(W_), C(C_), PR(PR_), place(size_t(C_ + 1) * kMaxPat * 2, -1) {}
 
     // Those that accept the fewest cells of a typical map first: one tile per cell, a wall on three
-    // cells in ten, the other tiles alike, one player (and its force) on the map.
+    // cells in ten, the other tiles alike, one player (and its force) on the map.  (Only an order:
+    // on maps of another kind the probe rejects less and results are the same.)
     void merge(const uint32_t *ent, int cnt) {
         const float few = 1.f / float(H * W), other = 0.7f / float(std::max(1, C - 2));
         out.clear();
