@@ -79,7 +79,8 @@ typedef enum {
                                rule's rarest entries at once, so only rules that can match
                                are visited.  On maps above 32 rows, in parallel rule order,
                                with 4 B waves within the device's wave slots, three more
-                               waves per environment share the probe and the matching.
+                               waves per environment share the probe, the matching and the
+                               write.
                                Needs R + 4 <= 64 and, within 64 KiB of LDS, (3 C + 4) planes
                                of H + 16 rows plus R + 4 match planes of H + 32 rows (4 bytes
                                per row for W <= 32, else 8), 36 bytes per rule and 96 more;
