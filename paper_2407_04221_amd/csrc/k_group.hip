@@ -34,7 +34,7 @@
 //
 // LDS (32-bit rows):
 //   P    [C+1][PR]     the map and the force plane (channel C); PR = HR + PAD rounded up to 4
-//                      rows (PAD: the largest pattern's rows - 1, and at least the 1 of the two-row
+//                      rows (PAD: the largest pattern's rows - 1, at least the 1 of the two-row
 //                      built-in moves), so a lane reads row y + i of any pattern entry without a
 //                      bounds test (rows H .. PR - 1 stay zero)
 //   M    [R+5][PR]     match planes, row y at PAD + y: the zero rows above let a vote read
@@ -111,16 +111,15 @@ constexpr int kMaxChan = 32;            // channels with a vote list
 constexpr int kKeyCells = 8;            // cells of a row one lane holds keys for
 constexpr int kShortLaunch = 16;        // launches of fewer steps read the lists from memory
 
-// Rows of the tallest pattern beyond its first, the built-in moves (two rows) among the patterns:
-// with loaded patterns of one row, too, the moves' votes read the match row above a cell's.
-__host__ __device__ constexpr int group_pad(int max_pat_h) {
-    return max_pat_h > 2 ? max_pat_h - 1 : 1;
-}
 // Words per plane row block: HR rows plus the pattern rows hanging below the last one,
 // rounded up to 4 (16-byte aligned table after the planes).
-__host__ __device__ constexpr int group_plane_words(int rows, int max_pat_h) {
-    return (rows + group_pad(max_pat_h) + 3) & ~3;
+__host__ __device__ constexpr int group_plane_words(int rows, int pat_rows) {
+    return (rows + pat_rows - 1 + 3) & ~3;
 }
+// Rows of the tallest pattern, the built-in moves (two rows) among the patterns: with loaded
+// patterns of one row, too, the moves' votes read the match row above a cell's.  The host lays out
+// the planes by it and gives it to the kernel as max_pat_h.
+constexpr int pattern_rows(int max_pat_h) { return max_pat_h > 2 ? max_pat_h : 2; }
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __host__ __device__ constexpr int key_stride(int W) { return W | 1; }
 // Words of a table's head (PT and RS), rounded up to 4.
@@ -288,7 +287,7 @@ __global__ void __launch_bounds__(64, WAVES) group_step(StepArgs a) {
     const int NC = SEQ ? C1 : C;
     // pattern rows beyond a lane's row: plane rows y + i and match rows y - i, i <= PAD, are
     // read without a bounds test
-    const int PAD = group_pad(a.max_pat_h);
+    const int PAD = a.max_pat_h - 1;
     const int PR = group_plane_words(HR, a.max_pat_h), MS = PR;
     const int s = a.per_env ? b : 0;
     const int nl = Rt - kMoveRules;               // loaded rules
@@ -548,7 +547,7 @@ __global__ void __launch_bounds__(64, WAVES) group_step(StepArgs a) {
             }
             Dd[h] = t[h];
         }
-        for (int i = 1; i < a.max_pat_h; ++i) {
+        for (int i = 1; i <= PAD; ++i) {
             next_rows<RPL>(t, t, y);
 #pragma unroll
             for (int h = 0; h < RPL; ++h) Dd[h] |= t[h];
@@ -893,7 +892,7 @@ __global__ void __launch_bounds__(64, WAVES) group_step(StepArgs a) {
 #pragma unroll
         for (int h = 0; h < RPL; ++h)
             rows |= uint32_t(__builtin_amdgcn_ballot_w64(fm[h] != 0u) & 0xFFFFull) << (kHq * h);
-        const int last = min(31 - __builtin_clz(rows) + a.max_pat_h - 1, HR - 1);
+        const int last = min(31 - __builtin_clz(rows) + PAD, HR - 1);
         int from = 0, past = HR;                  // the rows written
         if (!window(rows | (1u << last))) {
             from = r0;
@@ -1245,7 +1244,7 @@ __global__ void __launch_bounds__(64, WAVES) group_step(StepArgs a) {
 // LDS of a launch without the table's lists.
 size_t group_base_bytes(int H, int W, int C, int rules_per_set, int max_pat_h, bool sequential,
                         bool control, bool random) {
-    const int HR = group_rows(H), PR = group_plane_words(HR, max_pat_h);
+    const int HR = group_rows(H), PR = group_plane_words(HR, pattern_rows(max_pat_h));
     return sizeof(uint32_t) *
            (size_t(C + 1) * PR + size_t(rules_per_set + 1) * PR * (control ? 2 : 1) +
             size_t(rules_per_set - kMoveRules + 1) * HR +
@@ -1264,7 +1263,8 @@ bool group_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, int m
     // (rule masks are 64-bit; merged entries address rows of the stored and force planes in 12
     // bits: at most 1536 within these limits, and the LDS set at most 33 KiB)
     return rules_per_set <= 64 && C <= kMaxChan &&
-           (C + 1) * group_plane_words(group_rows(H), max_pat_h) <= kMaxEntryOffset + 1 &&
+           (C + 1) * group_plane_words(group_rows(H), pattern_rows(max_pat_h)) <=
+               kMaxEntryOffset + 1 &&
            group_base_bytes(H, W, C, rules_per_set, max_pat_h, false, false, false) <=
                size_t(kLdsBudget);
 }
@@ -1275,7 +1275,7 @@ bool group_mode_eligible(int H, int W, int C, int rules_per_set, int max_pat_h, 
     // as above; a vote list's places and a set's entries are 16-bit, and in sequential order only
     // one rule's votes are counted at a time
     const long cells = long(max_pat_h) * max_pat_w;
-    const int PR = group_plane_words(group_rows(H), max_pat_h);
+    const int PR = group_plane_words(group_rows(H), pattern_rows(max_pat_h));
     if (rules_per_set > 64 || (sequential ? 1 : rules_per_set) * cells > 254) return false;
     if (long(rules_per_set) * (C + 1) * cells > 0xFFFF || C + 1 > kMaxChan) return false;
     if (long(rules_per_set + 1) * PR * 4 > 0xFFFF) return false;
@@ -1331,7 +1331,7 @@ struct EntryMerger {
 void compile_group_tables(const GenericProgram &p, int H, int W, int C, int lists, int max_pat_h,
                           std::vector<uint32_t> &tab, int &stride, int &entry_words) {
     const int Rt = p.rules_per_set, C1 = C + 1;
-    const int PR = group_plane_words(group_rows(H), max_pat_h), PAD = group_pad(max_pat_h);
+    const int PAD = pattern_rows(max_pat_h) - 1, PR = group_plane_words(group_rows(H), PAD + 1);
     const int head = group_head_words(Rt, lists);
     EntryMerger em(H, W, C, PR);
     std::vector<uint32_t> merged;                 // every rule's entries, one after another
@@ -1431,7 +1431,9 @@ int device_simds() {
 }
 }  // namespace
 
-hipError_t launch_group_step(const StepArgs &a, hipStream_t s) {
+hipError_t launch_group_step(const StepArgs &step, hipStream_t s) {
+    StepArgs a = step;
+    a.max_pat_h = pattern_rows(a.max_pat_h);
     const int Rt = a.prog.rules_per_set, NC = a.sequential ? a.C + 1 : a.C;
     size_t lds = group_base_bytes(a.H, a.W, a.C, Rt, a.max_pat_h, a.sequential != 0,
                                   a.ctl.active != 0, a.ctl.random != 0);
